@@ -84,35 +84,26 @@ spade_status spade_model_set_attn_grouped(spade_model m, int mode);
  * returns SPADE_EINVAL. */
 spade_status spade_model_set_prefill_rows(spade_model m, int rows);
 
-/* Projection GEMM of forwards with many rows (prefill: hundreds to thousands
- * of prompt rows; bf16 weights).  A workgroup of eight waves owns 128 rows and
- * 256 columns and runs the k-loop in 32-k steps: the activations' step
- * through an LDS ring filled by direct loads, the weights' straight into
- * registers, so each weight byte is multiplied with 128 rows and each
- * activation byte read from LDS with 256 columns.  mode 0 (the default) uses
- * it for the QKV, O, gate/up and down projections once a launch has at least
- * one such workgroup per compute unit; mode 1 turns it off (the wide-row GEMM
- * runs instead); mode 2 uses it for every launch of more than 16 rows but
- * the LM head.  Results are bit-for-bit the same under every mode.  Other
- * values return SPADE_EINVAL. */
+/* Tiled GEMM of forwards of more than 144 rows (prefill; bf16 weights): a
+ * workgroup of eight waves owns up to 96 rows and 256 columns, or up to 144
+ * rows and 128 columns, the activations pass through an LDS ring filled by
+ * direct loads and the weights go straight into registers.  mode 0 (the
+ * default) uses it for every launch; mode 1 turns it off (the wide-row GEMM
+ * runs instead); mode 2 uses it for every projection launch of more than 16
+ * rows.  Results are bit-for-bit the same under every mode.  Other values
+ * return SPADE_EINVAL. */
 spade_status spade_model_set_big_gemm(spade_model m, int mode);
 
-/* Projection GEMM of batched verification calls of up to 144 rows (e.g. 16
- * requests of gamma + 1 = 9 rows; bf16 weights).  A workgroup of eight waves
- * owns every row of the call and 256 columns, so each weight byte enters one
- * compute unit once per launch; the k-loop runs in 32-k steps with the
- * activations' step in an LDS ring filled by direct loads and the weights'
- * straight into registers.  The k-loop is split over 1-8 workgroups per
- * panel group (whole k-ranges of the eight); each stores its sums in the
- * workspace, and a second launch, one workgroup per panel group and 16-row
- * tile, adds them in range order and runs the epilogue.  mode 0 (the
- * default) uses it where it measured faster than the wide-row GEMM: the
- * gate/up projection of 113 to 144 rows, the O projection of 129 to 144, the
- * down projection of 137 to 144; mode 1 turns it off (the wide-row GEMM runs
- * instead); mode 2 uses it for every QKV, O, gate/up and down launch of 17
- * to 144 rows.  k_splits 0 chooses the split count per launch, 1..8 fixes
- * it.  Results are bit-for-bit the same under every setting.  Other values
- * return SPADE_EINVAL. */
+/* The same GEMM for forwards of 17 to 144 rows (batched verification; bf16
+ * weights).  Where its workgroups leave compute units idle the k-loop is
+ * split over 1-8 workgroups per tile (whole k-ranges of the eight); each
+ * stores its sums in the workspace, and a second launch adds them in range
+ * order and runs the epilogue.  mode 0 (the default) uses it where it
+ * measured faster than the wide-row GEMM (more than 32 rows); mode 1 turns
+ * it off; mode 2 uses it for every QKV, O, gate/up and down launch.  k_splits
+ * 0 chooses the split count per launch, 1..8 fixes it.  Results are
+ * bit-for-bit the same under every setting.  Other values return
+ * SPADE_EINVAL. */
 spade_status spade_model_set_mid_gemm(spade_model m, int mode, int k_splits);
 
 /* K splitting of the batched O and down projections on the wide-row GEMM.

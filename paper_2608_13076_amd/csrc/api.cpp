@@ -101,8 +101,8 @@ ArenaLayout layout_of(const Dims& D) {
 
 struct WsPlan {
   size_t x, act_n, act_o, act_f, ssq, q, attn_o, attn_ml, attn_cnt, logits, stats, rope, err, split_cnt,
-      split_part, wide_cnt, wide_part, mid_part, corr_lse, corr_part, corr_cnt, prefill_tok, prefill_cnt, prefill_base, total;
-  size_t wide_items, wide_floats, mid_items;
+      split_part, wide_cnt, wide_part, tile_part, corr_lse, corr_part, corr_cnt, prefill_tok, prefill_cnt, prefill_base, total;
+  size_t wide_items, wide_floats, tile_floats;
   int max_units;
   size_t act_split, actf_split;
   int Mmax, Mrows, NCmax, Rmax;
@@ -158,11 +158,11 @@ WsPlan plan_ws(const Dims& D, int max_batch, int max_gamma, int max_len) {
   }
   p.wide_cnt = take(p.wide_items * 4);
   p.wide_part = take(p.wide_floats * 4);
-  // medium-M projections (forwards of 17 to 144 rows): one block of published
-  // sums per 256-column panel group of the widest projection
+  // k-split launches of the tiled GEMM (forwards of more than 16 rows): the
+  // widest projection of 144 rows, or a narrower one of more rows
   if (wb && p.Mrows > kWideMinRows)
-    p.mid_items = (size_t)((std::max(D.d + 2 * D.dkv, 2 * D.F) / 16 + 15) / 16);
-  p.mid_part = take(p.mid_items * mid_split_floats() * 4);
+    p.tile_floats = (size_t)((std::max(D.d + 2 * D.dkv, 2 * D.F) / 16 + 15) / 16) * tile_split_floats();
+  p.tile_part = take(p.tile_floats * 4);
   p.corr_lse = take((size_t)max_batch * 4);
   p.corr_part = take((size_t)max_batch * kCorrMaxSlices * 4 * 4);
   p.corr_cnt = take((size_t)max_batch * 4);
@@ -257,8 +257,8 @@ spade_status spade_model_create(const spade_config* cfg, void* d_weights, void* 
   w.wide_part = (float*)(b + p.wide_part);
   w.wide_items = p.wide_items;
   w.wide_floats = p.wide_floats;
-  w.mid_items = p.mid_items;
-  w.mid_part = p.mid_items > 0 ? (float*)(b + p.mid_part) : nullptr;
+  w.tile_floats = p.tile_floats;
+  w.tile_part = (float*)(b + p.tile_part);
   w.corr_lse = (float*)(b + p.corr_lse);
   w.corr_part = (float*)(b + p.corr_part);
   w.corr_cnt = (uint32_t*)(b + p.corr_cnt);

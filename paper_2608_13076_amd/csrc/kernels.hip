@@ -20,12 +20,10 @@
 //   gemm_wide_kernel   the same epilogues for more than 16 rows: row tiles
 //                  and panels per workgroup, the operand through an LDS ring,
 //                  optional k-splits for the O and down projections
-//   gemm_mid_kernel    batched-verification projections of up to 144 rows:
-//                  every row x 256 columns per workgroup, k-split, sums
-//                  published; gemm_mid_finish_kernel adds them in range
-//                  order and runs the epilogue
-//   gemm_big_kernel    the projections of prefill forwards (hundreds to
-//                  thousands of rows): 128 rows x 256 columns per workgroup
+//   gemm_tile_kernel   (gemm_tile.hip) launches of more than 32 rows: batched
+//                  verification and prefill forwards, up to 96 rows x 256 or
+//                  144 rows x 128 columns per workgroup; k-split launches
+//                  publish sums that gemm_tile_finish_kernel adds
 //   attn_lr_kernel the bf16 / head_dim-128 verify attention, one 256-key
 //                  chunk per workgroup; merges the chunks of a (request,
 //                  head) in the last one to finish, or leaves that to
@@ -50,8 +48,6 @@
 #include "device_accept.h"
 #include "device_attn.h"
 #include "device_gemm.h"
-#include "device_gemm_big.h"
-#include "device_gemm_mid.h"
 #include "device_gemm_split.h"
 #include "device_gemm_wide.h"
 
@@ -172,62 +168,6 @@ __global__ void __launch_bounds__(kGemmWaves * 64) gemm_split_kernel(GemmParams 
 // and k-splits of a unit group share that XCD's L2.  K-splits: cnt / part
 // hold one arrival counter / kWideItemFloats published values per (unit
 // group, row group).
-// Large-M projections (device_gemm_big.h): workgroup (row group, panel
-// group).  Workgroup b runs on XCD b % 8, which owns panel groups b % 8 + 8 c;
-// its workgroups go in blocks of 4 row groups x every one of its panel
-// groups, so the workgroups that run together on an XCD share both their
-// weight panels and their activation rows in its L2.
-template <int KIND>
-__global__ void __launch_bounds__(kBigWaves * 64)
-gemm_big_kernel(GemmParams a, int NRG, int NUG) {
-  extern __shared__ uint4 lds_dyn[];
-  const int b = (int)blockIdx.x, q = b >> 3;
-  const int NC = (NUG + 7) / 8;     // panel groups per XCD
-  constexpr int RB = 4;             // row groups per block
-  const int full = NRG / RB;        // whole blocks
-  int rg, c;
-  if (q < full * RB * NC) {
-    const int blk = q / (RB * NC), w = q - blk * (RB * NC);
-    c = w / RB;
-    rg = blk * RB + (w - c * RB);
-  } else {
-    const int rbs = NRG - full * RB, w = q - full * RB * NC;  // the last, partial block
-    c = w / rbs;
-    rg = full * RB + (w - c * rbs);
-  }
-  const int ug = (b & 7) + 8 * c;
-  if (ug >= NUG) return;  // uniform, before any barrier
-  GemmBig<KIND> gb(a, *(GemmBigSmem*)lds_dyn, rg, ug);
-  gb.run();
-}
-
-// Batched-verification projections of up to 144 rows
-// (device_gemm_mid.h), first pass: workgroup b = (panel group b / KS, k-split
-// b % KS) publishes its sums into part (kMidItemFloats per panel group).
-template <int KIND>
-__global__ void __launch_bounds__(kMidWaves * 64)
-gemm_mid_kernel(GemmParams a, int NUG, int KS, float* part) {
-  extern __shared__ uint4 lds_dyn[];
-  const int b = (int)blockIdx.x;
-  const int ug = b / KS, ks = b - ug * KS;
-  if (ug >= NUG) return;  // uniform, before any barrier
-  GemmMid<KIND> g(a, *(GemmMidSmem*)lds_dyn, ug, ks, KS, part + (size_t)ug * kMidItemFloats);
-  g.run();
-}
-
-// Second pass: workgroup b = (panel group b / kMidRT, row tile b % kMidRT)
-// adds the published sums in range order and runs the epilogue.
-template <int KIND>
-__global__ void __launch_bounds__(kMidWaves * 64)
-gemm_mid_finish_kernel(GemmParams a, int NUG, int KS, const float* part) {
-  __shared__ float rinv[16];
-  const int b = (int)blockIdx.x;
-  const int ug = b / kMidRT, mt = b - ug * kMidRT;
-  if (ug >= NUG || mt * 16 >= a.M) return;  // uniform, before any barrier
-  GemmMidFinish<KIND> f(a, rinv, ug, mt, KS, part);
-  f.run();
-}
-
 template <int RT, int P, int KIND, int KS, bool NT = true>
 __global__ void __launch_bounds__(kGemmWaves * 64)
     gemm_wide_kernel(GemmParams a, int NRG, int NUG, uint32_t* cnt, float* part) {
@@ -1160,43 +1100,6 @@ size_t wide_split_floats(int n_units, int M, int rt, int p) {
   return items * (size_t)8 * kGemmWaves * p * rt * 256;
 }
 
-size_t mid_split_floats() { return (size_t)kMidItemFloats; }
-
-// Rows above which a projection runs on the medium-M GEMM by default (the
-// wide-row GEMM's time grows with the rows, the medium-M GEMM's barely).
-int mid_min_rows(int kind) {
-  switch (kind) {
-    case GEMM_GU: return 112;
-    case GEMM_O: return 128;
-    case GEMM_DOWN: return 136;
-    default: return kMidRT * 16;  // QKV, LM head: never
-  }
-}
-
-// K-splits of a medium-M launch: the fewest that minimise the rounds of
-// workgroups (one per compute unit at a time) times the k-blocks of the
-// longest split, with a split launch charged about one and a half k-blocks
-// for the range partials it adds to what the second pass reads back.  A
-// fixed count (1-8) is used as given.
-int mid_k_splits(int n_units, int NKB, int n_cu, int fixed_ks) {
-  const int G = gemm_mid_unit_groups(n_units);
-  if (fixed_ks > 0) return std::min(fixed_ks, kMidMaxSplits);
-  int best = 1;
-  double best_cost = -1.0;
-  for (int ks = 1; ks <= kMidMaxSplits && ks <= NKB; ++ks) {
-    int longest = 0;
-    for (int s = 0; s < ks; ++s)
-      longest = std::max(longest, NKB * (8 * (s + 1) / ks) / 8 - NKB * (8 * s / ks) / 8);
-    const long rounds = ((long)G * ks + n_cu - 1) / n_cu;
-    const double cost = (double)rounds * longest + (ks > 1 ? 1.5 : 0.0);
-    if (best_cost < 0 || cost < best_cost - 1e-9) {
-      best_cost = cost;
-      best = ks;
-    }
-  }
-  return best;
-}
-
 WideChoice wide_choice(int kind, int M, int n_units, int NKB, int K, int n_cu, int fixed_rt, int fixed_p, int fixed_ks,
                        size_t cap_items, size_t cap_floats) {
   const int tiles = (M + 15) / 16;
@@ -1283,6 +1186,16 @@ hipError_t launch_wide(spade_model md, int kind, const GemmParams& gp, hipStream
   }
 }
 
+// Rows up to which the batched-verification settings (spade_model_set_mid_gemm)
+// govern the tiled GEMM; above, spade_model_set_big_gemm.
+constexpr int kTileMidRows = 144;
+
+// Whether a launch runs on the tiled GEMM by default.  Wide-row against tiled
+// (us per launch): 7B gate/up 39 / 41 at 28 rows, 54 / 47 at 49, 97 / 72 at
+// 144; O 16 / 14, 20 / 17, 31 / 23; 33B gate/up 91 / 93 at 28 rows, 141 / 105
+// at 49; LM heads even at 28 rows, 8B 289 / 197 at 49.
+bool tile_wins(int M) { return M > 32; }
+
 hipError_t launch_attn_prefill(const AttnParams& ap, bool abf16, hipStream_t st) {
   constexpr int W = kPrefillAttnTiles, SK = kPrefillAttnKeys;
   const int most = (int)attn_prefill_dyn_bytes(W, kAttnMaxChunks);
@@ -1299,56 +1212,6 @@ hipError_t launch_attn_prefill(const AttnParams& ap, bool abf16, hipStream_t st)
   if (abf16) hipLaunchKernelGGL((attn_prefill_kernel<true, W, SK>), grid, dim3(64 * W), dyn, st, ap, ngrp);
   else hipLaunchKernelGGL((attn_prefill_kernel<false, W, SK>), grid, dim3(64 * W), dyn, st, ap, ngrp);
   return hipGetLastError();
-}
-
-template <int KIND>
-hipError_t launch_big_kind(const GemmParams& gp, hipStream_t st) {
-  const void* fn = reinterpret_cast<const void*>(&gemm_big_kernel<KIND>);
-  static hipError_t attr =
-      hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(GemmBigSmem));
-  if (attr != hipSuccess) return attr;
-  const int nrg = gemm_big_row_groups(gp.M), nug = gemm_big_unit_groups(gp.n_units);
-  const int grid = 8 * ((nug + 7) / 8) * nrg;
-  hipLaunchKernelGGL((gemm_big_kernel<KIND>), dim3(grid), dim3(kBigWaves * 64), sizeof(GemmBigSmem), st, gp, nrg,
-                     nug);
-  return hipGetLastError();
-}
-
-template <int KIND>
-hipError_t launch_mid_kind(const GemmParams& gp, int ks, float* part, hipStream_t st) {
-  const void* fn = reinterpret_cast<const void*>(&gemm_mid_kernel<KIND>);
-  static hipError_t attr =
-      hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(GemmMidSmem));
-  if (attr != hipSuccess) return attr;
-  if (gp.M > kMidRT * 16 || ks < 1 || ks > kMidMaxSplits) return hipErrorInvalidValue;
-  const int nug = gemm_mid_unit_groups(gp.n_units);
-  hipLaunchKernelGGL((gemm_mid_kernel<KIND>), dim3(nug * ks), dim3(kMidWaves * 64), sizeof(GemmMidSmem), st, gp, nug,
-                     ks, part);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((gemm_mid_finish_kernel<KIND>), dim3(nug * kMidRT), dim3(kMidWaves * 64), 0, st, gp, nug, ks,
-                     (const float*)part);
-  return hipGetLastError();
-}
-
-hipError_t launch_mid(int kind, const GemmParams& gp, int ks, float* part, hipStream_t st) {
-  switch (kind) {
-    case GEMM_QKV: return launch_mid_kind<GEMM_QKV>(gp, ks, part, st);
-    case GEMM_O: return launch_mid_kind<GEMM_O>(gp, ks, part, st);
-    case GEMM_GU: return launch_mid_kind<GEMM_GU>(gp, ks, part, st);
-    case GEMM_DOWN: return launch_mid_kind<GEMM_DOWN>(gp, ks, part, st);
-    default: return hipErrorInvalidValue;
-  }
-}
-
-hipError_t launch_big(int kind, const GemmParams& gp, hipStream_t st) {
-  switch (kind) {
-    case GEMM_QKV: return launch_big_kind<GEMM_QKV>(gp, st);
-    case GEMM_O: return launch_big_kind<GEMM_O>(gp, st);
-    case GEMM_GU: return launch_big_kind<GEMM_GU>(gp, st);
-    case GEMM_DOWN: return launch_big_kind<GEMM_DOWN>(gp, st);
-    default: return hipErrorInvalidValue;
-  }
 }
 
 template <int HD, int RMAX>
@@ -1458,40 +1321,31 @@ hipError_t launch_layer_gemm(spade_model md, spade_kv kv, int kind, int layer, c
   }
   const int grid = std::min(units, md->gemm_wgs);
   g.NU = grid;  // LM head: one statistics entry per workgroup and row
-  if (wb && M > kWideMinRows && kind != GEMM_LM && md->big_gemm != 1) {
-    // many rows (prefill): 128-row x 256-column workgroups, once there are
-    // enough of them to fill the chip (or always, when forced)
-    const long wgs = (long)gemm_big_row_groups(M) * gemm_big_unit_groups(units);
-    if (md->big_gemm == 2 || wgs >= md->n_cu) {
-      GemmParams gp = g;
-      gp.w = wmat;
-      gp.NKB = K / KBd;
-      gp.n_units = units;
-      gp.M = M;
-      gp.m0 = 0;
-      gp.act = act;
-      gp.act_split = act_split;
-      gp.act_stride = K;
-      return launch_big(kind, gp, st);
+  if (wb && M > kWideMinRows) {
+    // more than 16 rows: the tiled GEMM where its estimate beats the wide-row
+    // GEMM's measured range (tile_wins), unless a setting turns it off or
+    // fixes the other engine's schedule; the LM head only where the accept
+    // step expects per-panel statistics
+    const bool lm = kind == GEMM_LM;
+    int mode = M <= kTileMidRows ? md->mid_gemm : md->big_gemm;
+    if (md->big_gemm == 2 || mode == 2) mode = lm ? 0 : 2;
+    const bool wide_fixed = md->wide_rt > 0 || md->wide_p > 0 || md->wide_ks > 0;
+    if (mode != 1 && !(lm && md->wide_rt < 0) && (mode == 2 || !wide_fixed)) {
+      const TileChoice c = tile_choice(kind, M, units, K / KBd, md->n_cu, M <= kTileMidRows ? md->mid_ks : 0,
+                                       W.tile_floats);
+      if (mode == 2 || md->wide_rt < 0 || tile_wins(M)) {
+        GemmParams gp = g;
+        gp.w = wmat;
+        gp.NKB = K / KBd;
+        gp.n_units = units;
+        gp.M = M;
+        gp.m0 = 0;
+        gp.act = act;
+        gp.act_split = act_split;
+        gp.act_stride = K;
+        return launch_tile(kind, gp, c, W.tile_part, st);
+      }
     }
-  }
-  // batched verification: every row in one workgroup per panel group (by
-  // default the gate/up projection of more than 112 rows, O and down of
-  // more than 128 and 136: the crossovers with the wide-row GEMM measured at
-  // the 7B shape; the QKV projection measured no faster)
-  if (wb && M > kWideMinRows && M <= kMidRT * 16 && kind != GEMM_LM && md->mid_gemm != 1 &&
-      (md->mid_gemm == 2 || M > mid_min_rows(kind)) && W.mid_part && (size_t)gemm_mid_unit_groups(units) <= W.mid_items) {
-    GemmParams gp = g;
-    gp.w = wmat;
-    gp.NKB = K / KBd;
-    gp.n_units = units;
-    gp.M = M;
-    gp.m0 = 0;
-    gp.act = act;
-    gp.act_split = act_split;
-    gp.act_stride = K;
-    const int ks = mid_k_splits(units, gp.NKB, md->n_cu, md->mid_ks);
-    return launch_mid(kind, gp, ks, W.mid_part, st);
   }
   if (wb && M > kWideMinRows && md->wide_rt >= 0) {
     // batched rows: every row in one launch, weights streamed once

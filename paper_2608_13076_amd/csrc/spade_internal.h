@@ -132,8 +132,8 @@ struct Workspace {
   uint32_t* wide_cnt;   // [wide_items] arrival counters of the k-split wide-row GEMM (kept at zero between calls)
   float* wide_part;     // [wide_floats] its published sums and range partials
   size_t wide_items, wide_floats;
-  float* mid_part;      // [mid_items][kMidItemFloats] sums published by the medium-M GEMM (null: engine off)
-  size_t mid_items;
+  float* tile_part;     // [tile_floats] sums published by the k-split launches of the tiled GEMM
+  size_t tile_floats;
   float* corr_lse;      // [Bmax] log-sum-exp of each sampling request's correction row
   float* corr_part;     // [Bmax][kCorrMaxSlices][4] per-slice winners of the correction draw
   uint32_t* corr_cnt;   // [Bmax] arrival counters of the correction slices (kept at zero between calls)
@@ -168,8 +168,8 @@ struct spade_model_s {
   int attn_grouped;  // grouped-query chunks (one workgroup per K/V head and chunk): 0 where they apply, 1 off
   int corr_split;  // correction draws of sampling requests: 0/2 over vocabulary slices, 1 in the accept workgroup
   int prefill_rows;  // prompt rows per request of a prefill forward: 0 as many as the workspace holds, else at most this
-  int big_gemm;  // large-M projection GEMM: 0 where it fills the chip, 1 off, 2 whenever more than 16 rows
-  int mid_gemm;  // medium-M GEMM: 0 O, gate/up, down above mid_min_rows (to 144 rows), 1 off, 2 every projection of 17-144
+  int big_gemm;  // tiled GEMM above 144 rows: 0 chosen, 1 off, 2 every projection of more than 16 rows
+  int mid_gemm;  // tiled GEMM of 17 to 144 rows: 0 chosen, 1 off, 2 every projection
   int mid_ks;    // its k-splits: 0 chosen per launch, 1..8 fixed
 };
 
@@ -224,9 +224,15 @@ struct WideChoice {
 WideChoice wide_choice(int kind, int M, int n_units, int NKB, int K, int n_cu, int fixed_rt, int fixed_p, int fixed_ks,
                        size_t cap_items, size_t cap_floats);
 size_t wide_split_floats(int n_units, int M, int rt, int p);
-int mid_k_splits(int n_units, int NKB, int n_cu, int fixed_ks);
-int mid_min_rows(int kind);  // rows above which a projection kind runs on the medium-M GEMM by default
-size_t mid_split_floats();  // published floats per panel group of a medium-M launch
+// tile of a tiled-GEMM launch: 16-row tiles and panels per wave of a workgroup, k-splits, estimated time
+struct TileChoice {
+  int rt, p, ks;
+  double us;
+};
+TileChoice tile_choice(int kind, int M, int n_units, int NKB, int n_cu, int fixed_ks, size_t cap_floats);
+size_t tile_split_floats();
+struct GemmParams;
+hipError_t launch_tile(int kind, const GemmParams& gp, const TileChoice& c, float* part, hipStream_t st);
 int lm_stats_panels(spade_model m, int M);
 hipError_t launch_softmax(const float* logits, int rows, int V, float invT, float* out, hipStream_t st);
 hipError_t launch_prefill_batch(spade_model md, spade_kv kv, int B, const int32_t* tokens, int ld,
