@@ -11,9 +11,10 @@ namespace spade {
 
 struct AcceptParams {
   const float* logits;
-  const float* stats;
+  const float* stats;  // (max, sum exp, argmax) entries: NU per row, rows stat_stride floats apart; NULL: scan the logits
   int NU;
-  int panels;  // 0: stats holds NU workgroup entries per row; > 0: one entry per panel
+  int stat_stride;
+  int given;           // the entries are row_stats_kernel's, of logits the caller computed
   int B, V, gamma, R;
   const int32_t* drafts;
   const float* q;
@@ -86,7 +87,111 @@ __device__ __forceinline__ bool accept_samples(const AcceptParams& p, int b) {
   return p.mode[b] == SPADE_SAMPLE && p.u != nullptr && (p.gamma == 0 || p.q != nullptr);
 }
 
+// (max, sum exp, argmax) of z = logit / T over tokens [v0, v1) of a row, by
+// all NT threads of the workgroup, 16 tokens per thread and step (16-byte
+// loads where the row allows them): the step's maximum first, then one
+// exponential per token.  NaN is skipped; ties keep the lower id.  Every
+// thread of a wave gets its wave's result.
+template <int NT, bool COH>
+__device__ __forceinline__ RowStat scan_stats(const float* row, int v0, int v1, float invT) {
+  const int tid = threadIdx.x;
+  const bool vec = !COH && ((size_t)(row + v0) & 15u) == 0u;
+  RowStat st{-INFINITY, 0.f, 0x7fffffff};
+  for (int base = v0; base < v1; base += NT * 16) {
+    float z[16];
+    int id0[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int v = base + (j * NT + tid) * 4;
+      id0[j] = v;
+      if (vec && v + 3 < v1) {
+        const float4 x = *(const float4*)(row + v);
+        z[4 * j] = x.x;
+        z[4 * j + 1] = x.y;
+        z[4 * j + 2] = x.z;
+        z[4 * j + 3] = x.w;
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) z[4 * j + i] = v + i < v1 ? ld_any<COH>(row + v + i) : __uint_as_float(0x7fc00000u);
+      }
+    }
+    float m = -INFINITY;
+    int a = 0x7fffffff;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      z[k] *= invT;
+      const int id = id0[k >> 2] + (k & 3);
+      // (ids ascend, so an equal later one is never lower)
+      if (z[k] > m || (z[k] == m && a == 0x7fffffff)) {
+        m = z[k];
+        a = id;
+      }
+    }
+    float e = 0.f;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) e += z[k] == m ? 1.f : (z[k] < m ? expf(z[k] - m) : 0.f);
+    if (a != 0x7fffffff) st = merge_stat(st, RowStat{m, m == -INFINITY ? 1.f : e, a});
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    RowStat o;
+    o.m = __shfl_xor(st.m, off);
+    o.s = __shfl_xor(st.s, off);
+    o.a = __shfl_xor(st.a, off);
+    st = (threadIdx.x & off) ? merge_stat(o, st) : merge_stat(st, o);
+  }
+  return st;
+}
+
+// The skinny LM head's row statistics from the per-panel statistics of the
+// other engines, by the 256 threads of a workgroup per row, in place (the
+// row's first entry): its NU workgroup entries are rebuilt (workgroup q folds
+// panels q, q + NU, ... in order; requested sixteen at a time and then folded,
+// so the loads do not wait for one another) and merged as accept_request
+// merges entries, so decisions do not depend on the engine.  Folded in the
+// accept kernel, one workgroup per request, this took most of its 36 us for
+// 16 requests of 9 rows and 8016 panels.
+__device__ __forceinline__ void fold_panels(float* row, int panels, int NU, RowStat* ent) {
+  constexpr int kBatch = 16;
+  for (int q = threadIdx.x; q < NU; q += 256) {
+    RowStat one{-INFINITY, 0.f, 0x7fffffff};
+    for (int u0 = q; u0 < panels; u0 += kBatch * NU) {
+      RowStat ps[kBatch];
+#pragma unroll
+      for (int j = 0; j < kBatch; ++j) {
+        const int u = u0 + j * NU;
+        ps[j] = RowStat{-INFINITY, 0.f, 0x7fffffff};
+        if (u < panels) ps[j] = RowStat{row[u * 3], row[u * 3 + 1], __float_as_int(row[u * 3 + 2])};
+      }
+#pragma unroll
+      for (int j = 0; j < kBatch; ++j)
+        if (ps[j].m != -INFINITY) one = merge_stat(one, ps[j]);
+    }
+    ent[q] = one;
+  }
+  __syncthreads();
+  if (threadIdx.x >= 64) return;
+  const int lane = threadIdx.x;
+  RowStat st{-INFINITY, 0.f, 0x7fffffff};
+  for (int q = lane; q < NU; q += 64)
+    if (ent[q].m != -INFINITY) st = merge_stat(st, ent[q]);
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    RowStat o;
+    o.m = __shfl_xor(st.m, off);
+    o.s = __shfl_xor(st.s, off);
+    o.a = __shfl_xor(st.a, off);
+    st = (lane & off) ? merge_stat(o, st) : merge_stat(st, o);
+  }
+  if (lane == 0) {
+    row[0] = st.m;
+    row[1] = st.s;
+    row[2] = __int_as_float(st.a);
+  }
+}
+
 struct AcceptSmem {
+  RowStat scan[kMaxR][16];  // given logits only: per row and wave
   float rlse[kMaxR];
   int rarg[kMaxR];
   int x[kMaxR];                     // draft tokens (clamped)
@@ -121,52 +226,33 @@ __device__ __forceinline__ void accept_request(const AcceptParams& p, int b, Acc
     }
   }
 
+  if (p.stats == nullptr) {
+    // given logits: the whole workgroup scans each row (a greedy-only call
+    // uses no scratch; the others come with row_stats_kernel's slices).  16
+    // requests x 9 rows of 128256 logits took 816 us with a wave per row
+    for (int r = 0; r < R; ++r) {
+      const RowStat st = scan_stats<NT, COH>(lg + (size_t)r * V, 0, V, invT);
+      if (lane == 0) sm.scan[r][wave] = st;
+    }
+    __syncthreads();
+  }
+
   // row statistics over the vocabulary: wave r merges row r from the LM
-  // head's per-workgroup partials (or, without them, from the logits), in a
-  // fixed order
+  // head's per-workgroup partials, from the slices of row_stats_kernel or
+  // from the scan above, in a fixed order
   for (int r = wave; r < R; r += NWV) {
     RowStat st{-INFINITY, 0.f, 0x7fffffff};
-    if (p.stats != nullptr && p.panels > 0) {
-      // per-panel statistics: rebuild the NU workgroup entries of the skinny
-      // LM head (workgroup q folds panels q, q + NU, ... in order), then merge
-      // them exactly as below
-      // (the panels of an entry are requested sixteen at a time and then
-      // folded in order, so the loads do not wait for one another)
-      constexpr int kBatch = 16;
-      const float* sp = p.stats + (size_t)(b * R + r) * p.panels * 3;
-      for (int q = lane; q < p.NU; q += 64) {
-        RowStat one{-INFINITY, 0.f, 0x7fffffff};
-        for (int u0 = q; u0 < p.panels; u0 += kBatch * p.NU) {
-          RowStat ps[kBatch];
-#pragma unroll
-          for (int j = 0; j < kBatch; ++j) {
-            const int u = u0 + j * p.NU;
-            ps[j] = RowStat{-INFINITY, 0.f, 0x7fffffff};
-            if (u < p.panels)
-              ps[j] = RowStat{ld_any<COH>(sp + u * 3), ld_any<COH>(sp + u * 3 + 1),
-                              __float_as_int(ld_any<COH>(sp + u * 3 + 2))};
-          }
-#pragma unroll
-          for (int j = 0; j < kBatch; ++j)
-            if (ps[j].m != -INFINITY) one = merge_stat(one, ps[j]);
-        }
-        if (one.m != -INFINITY) st = merge_stat(st, one);
-      }
-    } else if (p.stats != nullptr) {
-      const float* sp = p.stats + (size_t)(b * R + r) * p.NU * 3;
+    if (p.stats != nullptr) {
+      const float* sp = p.stats + (size_t)(b * R + r) * p.stat_stride;
 #pragma unroll 8
       for (int q = lane; q < p.NU; q += 64) {
         const RowStat one{ld_any<COH>(sp + q * 3), ld_any<COH>(sp + q * 3 + 1),
                           __float_as_int(ld_any<COH>(sp + q * 3 + 2))};
-        if (one.m != -INFINITY) st = merge_stat(st, one);
+        // (given logits may be -inf throughout: the lowest id then)
+        if (one.m != -INFINITY || p.given) st = merge_stat(st, one);
       }
-    } else {
-#pragma unroll 8
-      for (int v = lane; v < V; v += 64) {
-        const float z = ld_any<COH>(lg + (size_t)r * V + v) * invT;
-        if (z != z) continue;
-        st = merge_stat(st, RowStat{z, 1.f, v});
-      }
+    } else if (lane < NWV) {
+      st = sm.scan[r][lane];
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {

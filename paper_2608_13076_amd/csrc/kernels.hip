@@ -761,6 +761,32 @@ attn_prefill_kernel(AttnParams p, int ngrp) {
 // Accept / reject and the correction draw (device_accept.h), one workgroup per
 // request.
 // ---------------------------------------------------------------------------
+// Statistics of given logits (spade_accept_from_logits) over slices of the
+// vocabulary: workgroup (slice, row) writes entry `slice` of the row.
+__global__ void __launch_bounds__(256) row_stats_kernel(AcceptParams p, int per, float* stats) {
+  __shared__ RowStat part[4];
+  const int row = (int)blockIdx.y, s = (int)blockIdx.x;
+  const float invT = accept_samples(p, row / p.R) ? p.inv_T : 1.0f;
+  const int v0 = s * per, v1 = min(p.V, v0 + per);
+  const RowStat w = scan_stats<256, false>(p.logits + (size_t)row * p.V, v0, v1, invT);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = w;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    RowStat st = part[0];
+    for (int i = 1; i < 4; ++i) st = merge_stat(st, part[i]);
+    float* o = stats + ((size_t)row * gridDim.x + s) * 3;
+    o[0] = st.m;
+    o[1] = st.s;
+    o[2] = __int_as_float(st.a);
+  }
+}
+
+// One workgroup per row (device_accept.h: fold_panels).
+__global__ void __launch_bounds__(256) fold_stats_kernel(float* stats, int panels, int NU) {
+  __shared__ RowStat ent[kMaxStatGroups];
+  fold_panels(stats + (size_t)blockIdx.x * panels * 3, panels, NU, ent);
+}
+
 constexpr int kAcceptThreads = 1024;
 
 __global__ void __launch_bounds__(kAcceptThreads) accept_kernel(AcceptParams p) {
@@ -1519,12 +1545,39 @@ hipError_t launch_forward(spade_model md, spade_kv kv, const ForwardCall& fc, hi
   return hipSuccess;
 }
 
+namespace {
+
+// Calls with given logits that may sample (their scratch is this call's
+// anyway): the rows' statistics over slices of the vocabulary first, in the
+// memory of the correction's per-slice winners (at most 1024 floats a request;
+// the correction launch comes after they are read).  Greedy-only calls use no
+// scratch and scan their rows in the accept workgroup.
+constexpr int kStatSliceTokens = 4096;
+
+void launch_row_stats(AcceptParams& p, hipStream_t st) {
+  const int S = std::min((p.V + kStatSliceTokens - 1) / kStatSliceTokens, kCorrMaxSlices * 4 / (3 * p.R));
+  if (S < 2 || (long)p.B * p.R > 65535) return;
+  const int per = ((p.V + S - 1) / S + 3) / 4 * 4;
+  hipLaunchKernelGGL(row_stats_kernel, dim3(S, p.B * p.R), dim3(256), 0, st, p, per, p.corr_part);
+  p.stats = p.corr_part;
+  p.NU = S;
+  p.stat_stride = 3 * S;
+  p.given = 1;
+}
+
+}  // namespace
+
 hipError_t launch_accept(spade_model md, const AcceptCall& ac, hipStream_t st) {
   AcceptParams p{};
   p.logits = ac.logits;
   p.stats = ac.stats;
   p.NU = ac.NU;
-  p.panels = ac.panels;
+  p.stat_stride = ac.NU * 3;
+  if (ac.stats != nullptr && ac.panels > 0) {
+    hipLaunchKernelGGL(fold_stats_kernel, dim3(ac.B * (ac.gamma + 1)), dim3(256), 0, st, ac.stats, ac.panels, ac.NU);
+    p.NU = 1;
+    p.stat_stride = ac.panels * 3;
+  }
   p.B = ac.B;
   p.V = ac.V;
   p.gamma = ac.gamma;
@@ -1547,6 +1600,7 @@ hipError_t launch_accept(spade_model md, const AcceptCall& ac, hipStream_t st) {
     p.corr_lse = md->ws.corr_lse;
     p.corr_part = md->ws.corr_part;
     p.corr_cnt = md->ws.corr_cnt;
+    if (p.stats == nullptr) launch_row_stats(p, st);
   }
   hipLaunchKernelGGL(accept_kernel, dim3(ac.B), dim3(kAcceptThreads), 0, st, p);
   if (split) {
@@ -1629,6 +1683,7 @@ hipError_t launch_accept_noalloc(const AcceptCall& ac, uint32_t* err, hipStream_
     p.corr_cnt = (uint32_t*)(base + offsetof(NoAllocScratch, cnt));
     p.corr_lse = (float*)(base + offsetof(NoAllocScratch, lse));
     p.corr_part = (float*)(base + offsetof(NoAllocScratch, part));
+    launch_row_stats(p, st);
   }
   hipLaunchKernelGGL(accept_kernel, dim3(ac.B), dim3(kAcceptThreads), 0, st, p);
   if (may_sample) {

@@ -204,7 +204,7 @@ struct ForwardCall {
 struct AcceptCall {
   int B, gamma, V;
   const float* logits;     // [B][gamma+1][V]
-  const float* stats;      // [B*(gamma+1)][NU][3] from the LM head, or NULL
+  float* stats;            // [B*(gamma+1)][NU][3] from the LM head, or NULL
   int NU;
   int panels;              // > 0: stats is [B*(gamma+1)][panels][3], one entry per panel
   const int32_t* drafts;
