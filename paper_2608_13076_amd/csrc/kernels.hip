@@ -838,6 +838,98 @@ __global__ void __launch_bounds__(256) softmax_rows_kernel(const float* logits, 
   for (int v = threadIdx.x; v < V; v += 256) o[v] = expf(z[v] * invT - m) * inv;
 }
 
+// Long rows, cut into slices of per tokens, one workgroup each: slice
+// maximum and sum (scratch: the first two floats of the slice's own output),
+// then per row the total of its slices, copied back to each of them, then the
+// outputs.  A 128256-token row took 280 us in one workgroup (a serial chain of
+// loads and exponentials on one compute unit).
+constexpr int kSoftmaxSlice = 4096, kSoftmaxMaxSlices = 256;
+
+// z[16] of this thread: tokens v0 + 4 (256 j + tid) + i of the slice, NaN-free
+// filler -inf past v1
+__device__ __forceinline__ void softmax_load(const float* row, int v0, int v1, float invT, bool vec, float (&z)[16]) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int v = v0 + (j * 256 + (int)threadIdx.x) * 4;
+    if (vec && v + 3 < v1) {
+      const float4 x = *(const float4*)(row + v);
+      z[4 * j] = x.x * invT;
+      z[4 * j + 1] = x.y * invT;
+      z[4 * j + 2] = x.z * invT;
+      z[4 * j + 3] = x.w * invT;
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) z[4 * j + i] = v + i < v1 ? row[v + i] * invT : -INFINITY;
+    }
+  }
+}
+
+__global__ void __launch_bounds__(256) softmax_slice_kernel(const float* logits, int V, int per, float invT, float* out) {
+  __shared__ float red[4];
+  const float* row = logits + (size_t)blockIdx.y * V;
+  const int v0 = (int)blockIdx.x * per, v1 = min(V, v0 + per);
+  const bool vec = (((size_t)(row + v0)) & 15u) == 0u;
+  float m = -INFINITY, s = 0.f;
+  for (int b = v0; b < v1; b += 4096) {
+    float z[16], c = -INFINITY;
+    softmax_load(row, b, v1, invT, vec, z);
+#pragma unroll
+    for (int k = 0; k < 16; ++k) c = fmaxf(c, z[k]);
+    const float nm = fmaxf(m, c);
+    s = m == -INFINITY ? s : s * expf(m - nm);
+    m = nm;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) s += z[k] == -INFINITY ? 0.f : expf(z[k] - m);
+  }
+  const float bm = block_reduce_256(m, true, red);
+  const float bs = block_reduce_256(m == -INFINITY ? s : s * expf(m - bm), false, red);
+  if (threadIdx.x == 0) {
+    float* o = out + (size_t)blockIdx.y * V + v0;
+    o[0] = bm;
+    o[1] = bs;
+  }
+}
+
+__global__ void __launch_bounds__(256) softmax_total_kernel(int V, int per, int S, float* out) {
+  __shared__ float red[4];
+  float* o = out + (size_t)blockIdx.x * V + (size_t)threadIdx.x * per;
+  const bool in = (int)threadIdx.x < S;
+  const float m = in ? o[0] : -INFINITY, s = in ? o[1] : 0.f;
+  const float bm = block_reduce_256(m, true, red);
+  const float bs = block_reduce_256(in ? s * expf(m - bm) : 0.f, false, red);
+  if (in) {
+    o[0] = bm;
+    o[1] = 1.0f / bs;
+  }
+}
+
+__global__ void __launch_bounds__(256) softmax_write_kernel(const float* logits, int V, int per, float invT, float* out) {
+  const float* row = logits + (size_t)blockIdx.y * V;
+  float* o = out + (size_t)blockIdx.y * V;
+  const int v0 = (int)blockIdx.x * per, v1 = min(V, v0 + per);
+  const bool vec = ((((size_t)(row + v0)) | ((size_t)(o + v0))) & 15u) == 0u;
+  const float m = o[v0], inv = o[v0 + 1];
+  __syncthreads();  // every thread has the totals before they are overwritten
+  for (int b = v0; b < v1; b += 4096) {
+    float z[16];
+    softmax_load(row, b, v1, invT, vec, z);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int v = b + (j * 256 + (int)threadIdx.x) * 4;
+      float e[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) e[i] = expf(z[4 * j + i] - m) * inv;
+      if (vec && v + 3 < v1) {
+        *(float4*)(o + v) = make_float4(e[0], e[1], e[2], e[3]);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (v + i < v1) o[v + i] = e[i];
+      }
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Small kernels: commit, lens advance, packing.
 // ---------------------------------------------------------------------------
@@ -1746,7 +1838,18 @@ hipError_t launch_pack(spade_model md, int kind, int layer, const void* src, hip
 }
 
 hipError_t launch_softmax(const float* logits, int rows, int V, float invT, float* out, hipStream_t st) {
-  hipLaunchKernelGGL(softmax_rows_kernel, dim3(rows), dim3(256), 0, st, logits, V, invT, out);
+  // slices from two of them on (every slice then holds more than 1000
+  // tokens); shorter rows, and more rows than a grid's y dimension, in one
+  // workgroup each
+  const int S = std::min(kSoftmaxMaxSlices, (V + kSoftmaxSlice - 1) / kSoftmaxSlice);
+  if (S < 2 || rows > 65535) {
+    hipLaunchKernelGGL(softmax_rows_kernel, dim3(rows), dim3(256), 0, st, logits, V, invT, out);
+    return hipGetLastError();
+  }
+  const int per = ((V + S - 1) / S + 3) / 4 * 4;
+  hipLaunchKernelGGL(softmax_slice_kernel, dim3(S, rows), dim3(256), 0, st, logits, V, per, invT, out);
+  hipLaunchKernelGGL(softmax_total_kernel, dim3(rows), dim3(256), 0, st, V, per, S, out);
+  hipLaunchKernelGGL(softmax_write_kernel, dim3(S, rows), dim3(256), 0, st, logits, V, per, invT, out);
   return hipGetLastError();
 }
 
