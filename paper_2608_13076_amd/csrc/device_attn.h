@@ -804,76 +804,56 @@ __device__ __forceinline__ void attn_publish_grp(const AttnItem& it, int kvh, in
 // Where the verify kernel spreads one chunk over eight waves, here one wave
 // runs a whole tile: the eight 32-key slices of a chunk one after another,
 // with no barrier between them.  The W waves of a workgroup take W
-// consecutive tiles of one (request, head) and share every K and V^T block:
-// SK keys at a time, staged through a two-slot LDS ring (rows of 16-byte
-// pieces XOR-swizzled by row, so the 16 rows a fragment read touches hit
-// distinct banks), the next block's loads in flight while the current one is
-// used.  Each chunk is walked twice: the first walk keeps every chunk's row
-// max and row sum in LDS, the merge weights follow from them, and the second
-// walk recomputes each chunk's probabilities, multiplies them with V and adds
-// the result, times its weight, to the tile's running sums in registers.
+// consecutive tiles of one (request, head) and share every K and V block: 64
+// keys (16 KB) at a time through an LDS ring of NS slots, filled by direct
+// buffer->LDS loads NS - 1 blocks ahead.  The cache holds K and V in MFMA
+// fragment order, so a block is 16 contiguous 1 KB fragments and a fragment
+// read is one conflict-free ds_read_b128; the ring is read with inline asm and
+// explicit waits (the compiler would wait for every fill in flight).
+//
+// The products are computed transposed (S^T = K Q^T, O^T = V^T P^T: the same
+// products summed over the same k order, so the same bits): a lane then holds
+// one query's column, the row maximum and sum are mostly in-lane (the adds of
+// row16_sum's butterfly, two of the four steps across lanes), and the
+// probabilities reach the second product's operand layout by two lane swaps
+// per register instead of through LDS.
+//
+// Each chunk is walked twice: the first walk keeps every chunk's row max and
+// row sum in LDS, the merge weights follow from them, and the second walk
+// recomputes the probabilities (the chunk's maximum known) block by block,
+// multiplies them with V and adds each chunk's result, times its weight, to
+// the tile's running sums in registers.
+//
+// What bounds it: the longest tile's chain of blocks for one prompt, VALU
+// (masks, exponentials, bf16 terms) and MFMA about evenly for many.  Staging
+// through registers with two slots, a barrier and a load's latency per block
+// and the probabilities through LDS took 99 us per layer for 1018 rows of 32
+// heads (253 for 2048 rows after up to 2048 more); this takes 52 (170).
 // ---------------------------------------------------------------------------
-template <int W, int SK>
-struct AttnPfSmem {
-  static_assert(SK == 64 || SK == 128, "staged blocks of 64 or 128 keys");
-  uint4 st[2][SK * 16];                    // K: SK rows of 16 pieces; V^T: 128 rows of SK / 8 pieces
-  uint16_t ph[W][16][40], pl[W][16][40];  // one 32-key step's probabilities, per wave (rows padded by 16 bytes)
-};
+constexpr int kPfBlock = 16384;  // bytes of a 64-key block of K or V
 
-// Dynamic LDS of the prefill attention: per wave, chunk and row a (max, sum)
-// pair, then the merge weight in .x.
-__host__ __device__ inline unsigned attn_prefill_dyn_bytes(int W, int NC) { return (unsigned)W * NC * 16 * 8; }
-
-// piece c (8 features) of staged K row r; piece c (8 keys) of staged V^T row f
-__device__ __forceinline__ int pf_k_at(int r, int c) { return r * 16 + (c ^ (r & 15)); }
-// The K piece that staging thread e moves: row r (a position of the block),
-// piece c, in the cache's fragment order (k_cache_index), so 64 consecutive
-// threads read one 1 KB fragment: 16 positions x 32 features.
-__device__ __forceinline__ void pf_k_piece(int e, int& r, int& c) {
-  const int fr = e >> 6, ln = e & 63;
-  r = 16 * (fr >> 2) + (ln & 15);
-  c = 4 * (fr & 3) + (ln >> 4);
-}
-template <int SK>
-__device__ __forceinline__ int pf_v_at(int f, int c) {
-  constexpr int CPR = SK / 8;
-  return f * CPR + (CPR == 16 ? (c ^ (f & 15)) : (c ^ ((f >> 1) & 7)));
+// Dynamic LDS: the ring, then per wave, chunk and row a pair: the chunk's row
+// max and row sum, later max and merge weight.
+__host__ __device__ inline unsigned attn_prefill_dyn_bytes(int W, int NS, int NC) {
+  return (unsigned)NS * kPfBlock + (unsigned)W * NC * 16 * 8;
 }
 
-// This thread's share of staged block b of chunk c: K (b < 256 / SK: keys
-// c * 256 + b * SK ..) or V^T (keys c * 256 + (b - 256 / SK) * SK ..).  Keys
-// at or past k_hi (V^T: 8-key pieces past ke) read as zero.
-template <int W, int SK>
-__device__ __forceinline__ void pf_fetch(int c, int b, int k_hi, int ke, const uint16_t* kc, const uint16_t* vc,
-                                         uint4 (&r)[SK * 16 / (64 * W)]) {
-  constexpr int PER = SK * 16 / (64 * W), NB = 256 / SK, CPR = SK / 8;
-  const bool is_v = b >= NB;
-  const int k0 = c * 256 + (is_v ? b - NB : b) * SK;
-#pragma unroll
-  for (int q = 0; q < PER; ++q) {
-    const int e = (int)threadIdx.x + 64 * W * q;
-    r[q] = make_uint4(0, 0, 0, 0);
-    if (!is_v) {
-      int row, pc;
-      pf_k_piece(e, row, pc);
-      if (k0 + row < k_hi) r[q] = *(const uint4*)(kc + k_cache_index(pc * 8, k0 + row, kAttnHd));
-    } else {
-      const int f = e / CPR, pc = e % CPR, key = k0 + 8 * pc;
-      if (key + 8 <= ke) r[q] = *(const uint4*)(vc + v_cache_index(f, key, kAttnHd));
-    }
-  }
+typedef uint32_t u32x4p __attribute__((ext_vector_type(4)));
+
+template <int F>
+__device__ __forceinline__ u32x4p pf_read(uint32_t addr) {
+  u32x4p v;
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(F * 1024));
+  return v;
 }
 
-template <int W, int SK>
-__device__ __forceinline__ void pf_stash(AttnPfSmem<W, SK>& s, int slot, int b, const uint4 (&r)[SK * 16 / (64 * W)]) {
-  constexpr int PER = SK * 16 / (64 * W), NB = 256 / SK, CPR = SK / 8;
-#pragma unroll
-  for (int q = 0; q < PER; ++q) {
-    const int e = (int)threadIdx.x + 64 * W * q;
-    int kr, kpc;
-    pf_k_piece(e, kr, kpc);
-    s.st[slot][b < NB ? pf_k_at(kr, kpc) : pf_v_at<SK>(e / CPR, e % CPR)] = r[q];
-  }
+// wait until at most N of the wave's LDS reads are outstanding; the eight
+// fragments depend on the wait
+template <int N>
+__device__ __forceinline__ void pf_wait(u32x4p (&x)[8]) {
+  asm volatile("s_waitcnt lgkmcnt(%8)"
+               : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7])
+               : "n"(N));
 }
 
 // Wave-local ordering of LDS traffic between the lanes of one wave.
@@ -883,29 +863,57 @@ __device__ __forceinline__ void pf_wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// lanes l, l ^ 16 (then ^ 32) combined in every lane
+__device__ __forceinline__ float pf_add16(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float pf_add32(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float pf_max4(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(t[0]), __uint_as_float(t[1]));
+}
+
+// Quads q (this lane's four keys 4 g ..) of two 16-key groups, one register
+// each, to octet order: lane group g gets keys 8 g .. + 3 in a, + 4 .. + 7 in
+// b of the 32 keys.
+__device__ __forceinline__ void pf_octet(uint32_t& a, uint32_t& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  const auto t = __builtin_amdgcn_permlane16_swap(r[0], r[1], false, false);
+  a = t[0];
+  b = t[1];
+}
+
 // q: this request's query rows ([R][d], head h's features at h * kAttnHd);
-// kc / vc: the K and V blocks of (request, K/V head); L: the request's
-// cached keys; t0: the group's first tile (tile t0 + wave for this wave).
-// out(row, dd, value) receives every output of the group's rows (row counted
-// from the request's first prompt row).  mlw: W * NCP * 16 pairs; NCP bounds
-// the chunks of any tile.  All 64 W threads call it.
-template <int W, int SK, class Out>
-__device__ __forceinline__ void attn_prefill_tiles(AttnPfSmem<W, SK>& s, float2* mlw, int NCP, const float* q,
-                                                   int d, int h, const uint16_t* kc, const uint16_t* vc, int L,
-                                                   int R, int t0, float scale, Out&& out) {
-  constexpr int NB = 256 / SK, SPB = SK / 32, PER = SK * 16 / (64 * W);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+// rk / rv: the K and V blocks of (request, K/V head), kv_stride positions; L:
+// the request's cached keys; t0: the group's first tile (tile t0 + wave for
+// this wave).  out4(row, dd, v) receives outputs dd .. dd + 3 of a row (counted
+// from the request's first prompt row).  lds: the ring, then W * NCP * 16
+// pairs; NCP bounds the chunks of any tile.  All 64 W threads call it.
+template <int W, int NS, class Out>
+__device__ __forceinline__ void attn_prefill_tiles(uint8_t* lds, int NCP, const float* q, int d, int h, Rsrc rk,
+                                                   Rsrc rv, int L, int R, int t0, float scale, Out&& out4) {
+  static_assert(W == 4, "a wave moves four of a block's 16 fragments");
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int g = lane >> 4, kl = lane & 15;
   const int ntile = (R + 15) / 16;
   const int tl = t0 + wave;                            // this wave's tile
   const int Rt = tl < ntile ? min(16, R - 16 * tl) : 0;  // its rows (0: idle)
   const int Lt = L + 16 * tl;
-  const int nct = Rt > 0 ? (Lt + Rt + 255) / 256 : 0;
+  const int end = Rt > 0 ? Lt + Rt : 0;                // its keys
   // the group's furthest key: the end of its last tile
   const int tlast = min(t0 + W, ntile) - 1;
   const int kend = L + 16 * tlast + min(16, R - 16 * tlast);
-  const int ncg = (kend + 255) / 256;
-  float2* ml = mlw + (size_t)wave * NCP * 16;
+  const int nk = (kend + 63) / 64;                     // 64-key blocks
+  float2* ml = (float2*)(lds + NS * kPfBlock) + (size_t)wave * NCP * 16;
+  const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) void*)lds;
+  const uint32_t frag = lds0 + (uint32_t)lane * 16u;
+  const uint32_t mla = lds0 + (uint32_t)(NS * kPfBlock) + (uint32_t)(wave * NCP * 16 + kl) * 8u;  // this lane's query
 
   // this lane's query fragments (row kl of the tile, features 32 ks + 8 g ..),
   // as two bf16 terms; rows past the tile: zeros
@@ -926,185 +934,308 @@ __device__ __forceinline__ void attn_prefill_tiles(AttnPfSmem<W, SK>& s, float2*
     }
   }
 
-  // scores of staged K block b (slices b * SPB ..) of chunk c into sv
-  auto scores = [&](const uint4* blk, int c, int b, float (&sv)[8][2][4]) {
-    const int k_lo = c * 256, k_hi = min(k_lo + 256, Lt + Rt);
-#pragma unroll
-    for (int j = 0; j < SPB; ++j) {
-      const int vw = b * SPB + j;  // the slice (the verify kernel's wave)
-#pragma unroll
-      for (int grp = 0; grp < 2; ++grp) {
-        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-        const int r = 32 * j + 16 * grp + kl;
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-          const uint4 kf = blk[pf_k_at(r, 4 * ks + g)];
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ql[ks]),
-                                                        __builtin_bit_cast(bf16x8, kf), acc, 0, 0, 0);
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, qh[ks]),
-                                                        __builtin_bit_cast(bf16x8, kf), acc, 0, 0, 0);
-        }
-        const int key = k_lo + 32 * vw + 16 * grp + kl;
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          sv[vw][grp][i] = (key < k_hi && key <= Lt + 4 * g + i) ? acc[i] * scale : -INFINITY;
-      }
-    }
-  };
-  // chunk softmax of sv: probabilities in place, and each row's max and sum
-  auto softmax = [&](float (&sv)[8][2][4], float (&m)[4], float (&l)[4]) {
+  // The block stream: nk K blocks (first walk), then K and V of each block in
+  // turn (second walk).  Block t goes to slot t % NS; wave w moves fragments
+  // 4 w .. + 3 (of V: feature tiles 2 w, 2 w + 1 at the block's two 32-key
+  // steps).  Blocks past the stream read zeros.
+  const int nt = 3 * nk;
+  auto fill = [&](int t) {
+    const bool first = t < nk;
+    const int r = t - nk, kb = first ? t : r >> 1;
+    const bool is_v = !first && (r & 1);
+    uint32_t off[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      float mw[8];
+      const int f = 4 * wave + i;
+      const uint32_t at = is_v ? (uint32_t)((kb >> 2) * 65536 + (f >> 1) * 8192 + ((kb & 3) * 2 + (f & 1)) * 1024)
+                               : (uint32_t)(kb * kPfBlock + f * 1024);
+      off[i] = t < nt ? at + (uint32_t)lane * 16u : kOob;
+    }
+    __attribute__((address_space(3))) uint8_t* dst =
+        (__attribute__((address_space(3))) uint8_t*)(lds + (t % NS) * kPfBlock + 4 * wave * 1024);
 #pragma unroll
-      for (int vw = 0; vw < 8; ++vw) mw[vw] = row16_max(fmaxf(sv[vw][0][i], sv[vw][1][i]));
-      const float M = fmaxf(fmaxf(fmaxf(mw[0], mw[1]), fmaxf(mw[2], mw[3])), fmaxf(fmaxf(mw[4], mw[5]), fmaxf(mw[6], mw[7])));
-      float lsum = 0.f, mm = -INFINITY;
-#pragma unroll
-      for (int vw = 0; vw < 8; ++vw) {
-        float sum = 0.f;
-#pragma unroll
-        for (int grp = 0; grp < 2; ++grp) {
-          const float e = (M == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((sv[vw][grp][i] - M) * 1.44269504088896341f);
-          sum += e;
-          sv[vw][grp][i] = e;
-        }
-        lsum += row16_sum(sum);
-        mm = fmaxf(mm, mw[vw]);
-      }
-      m[i] = mm;
-      l[i] = lsum;
+    for (int i = 0; i < 4; ++i) {
+      if (is_v) __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (__attribute__((address_space(3))) void*)(dst + i * 1024), 16, off[i], 0, 0, 0);
+      else __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (__attribute__((address_space(3))) void*)(dst + i * 1024), 16, off[i], 0, 0, 0);
     }
   };
+  // Block t: this wave's share has landed (the NS - 2 blocks after it have
+  // four loads each), every wave's after the barrier, which also ends every
+  // wave's reads of block t - 1; block t + NS - 1 goes into its slot.
+  auto step = [&](int t) {
+    wait_vmcnt<(NS - 2) * 4>();
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    fill(t + NS - 1);
+    __builtin_amdgcn_sched_barrier(0);
+  };
 
-  uint4 pre[PER];
-  // first walk: every chunk's row max and row sum
-  pf_fetch<W, SK>(0, 0, kend, 0, kc, vc, pre);
-  pf_stash(s, 0, 0, pre);
-  __syncthreads();
-  int slot = 0;
-  for (int c = 0; c < ncg; ++c) {
-    float sv[8][2][4];
+  // scaled, masked scores of the K block kb in slot t % NS: sv[u][i] of this
+  // lane's query with key 64 kb + 16 u + 4 g + i
+  auto scores = [&](int t, int kb, float (&sv)[4][4]) {
+    const uint32_t base = frag + (uint32_t)(t % NS) * (uint32_t)kPfBlock;
+    u32x4p xa[8], xb[8];  // features 32 ks ..: ks = 0, 1 of the four groups, then 2, 3
+    xa[0] = pf_read<0>(base);
+    xa[1] = pf_read<4>(base);
+    xa[2] = pf_read<8>(base);
+    xa[3] = pf_read<12>(base);
+    xa[4] = pf_read<1>(base);
+    xa[5] = pf_read<5>(base);
+    xa[6] = pf_read<9>(base);
+    xa[7] = pf_read<13>(base);
+    xb[0] = pf_read<2>(base);
+    xb[1] = pf_read<6>(base);
+    xb[2] = pf_read<10>(base);
+    xb[3] = pf_read<14>(base);
+    xb[4] = pf_read<3>(base);
+    xb[5] = pf_read<7>(base);
+    xb[6] = pf_read<11>(base);
+    xb[7] = pf_read<15>(base);
+    floatx4 acc[4];
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const bool more = b + 1 < NB || c + 1 < ncg;
-      if (more) pf_fetch<W, SK>(b + 1 < NB ? c : c + 1, b + 1 < NB ? b + 1 : 0, kend, 0, kc, vc, pre);
-      if (c < nct) scores(s.st[slot], c, b, sv);
-      if (more) pf_stash(s, slot ^ 1, 0, pre);
-      __syncthreads();
-      slot ^= 1;
+    for (int u = 0; u < 4; ++u) acc[u] = floatx4{0.f, 0.f, 0.f, 0.f};
+    auto mul = [&](const u32x4p (&x)[8], int ks0) {
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int term = 0; term < 2; ++term)
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                __builtin_bit_cast(bf16x8, x[4 * k + u]),
+                __builtin_bit_cast(bf16x8, term ? qh[ks0 + k] : ql[ks0 + k]), acc[u], 0, 0, 0);
+    };
+    pf_wait<8>(xa);
+    mul(xa, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    pf_wait<0>(xb);
+    mul(xb, 2);
+    const int k0 = 64 * kb + 4 * g;
+    if (64 * kb + 64 > Lt) {  // keys some row of the tile does not see
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int key = k0 + 16 * u + i;
+          sv[u][i] = (key < end && key <= Lt + kl) ? acc[u][i] * scale : -INFINITY;
+        }
+    } else {
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+#pragma clang fp contract(off)
+          sv[u][i] = acc[u][i] * scale;
+        }
     }
-    if (c < nct) {
-      float m[4], l[4];
-      softmax(sv, m, l);
+  };
+  auto prob = [](float sv, float M) {
+#pragma clang fp contract(off)
+    return __builtin_amdgcn_exp2f((sv - M) * 1.44269504088896341f);
+  };
+
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (kl == 0 && 4 * g + i < Rt) ml[c * 16 + 4 * g + i] = make_float2(m[i], l[i]);
+  for (int t = 0; t < NS - 1; ++t) fill(t);
+  // first walk: every chunk's row max and row sum
+  for (int c = 0; 4 * c < nk; ++c) {
+    float sv[4][4][4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const int kb = 4 * c + b;
+      if (kb >= nk) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) sv[b][u][i] = -INFINITY;
+        continue;
+      }
+      step(kb);
+      if (64 * kb < end) {
+        scores(kb, kb, sv[b]);
+      } else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) sv[b][u][i] = -INFINITY;
+      }
+    }
+    if (256 * c < end) {
+      float M = -INFINITY;
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) M = fmaxf(M, sv[b][u][i]);
+      M = pf_max4(M);
+      const float Mz = M == -INFINITY ? 0.f : M;  // an empty chunk: every probability exp2(-inf) = 0
+      float lsum = 0.f;
+#pragma unroll
+      for (int vw = 0; vw < 8; ++vw) {  // 32-key slices, each in row16_sum's order
+        float e[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          e[i] = prob(sv[vw >> 1][2 * (vw & 1)][i], Mz) + prob(sv[vw >> 1][2 * (vw & 1) + 1][i], Mz);
+        lsum += pf_add32(pf_add16((e[0] + e[1]) + (e[2] + e[3])));
+      }
+      if (g == 0) {
+        const uint64_t v = (uint64_t)__float_as_uint(M) | ((uint64_t)__float_as_uint(lsum) << 32);
+        asm volatile("ds_write_b64 %0, %1" ::"v"(mla + (uint32_t)c * 128u), "v"(v) : "memory");
+      }
     }
   }
-  // merge weights of this wave's rows, in place of (max, sum)
+  // merge weights of this wave's rows, in place of the row sums
+  const int nct = (end + 255) / 256;
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   pf_wave_sync();
-  for (int row = 0; row < Rt; ++row)
-    attn_row_weights(
-        nct,
-        [&](int c, bool ok, float& m, float& l) {
-          const float2 v = ok ? ml[c * 16 + row] : make_float2(0.f, 0.f);
-          m = v.x;
-          l = v.y;
-        },
-        [&](int c, float w) { ml[c * 16 + row].x = w; });
+  if (nct <= 16) {
+    // attn_row_weights for this lane's row: the same terms, the adds of its
+    // butterfly over lanes (chunk c in lane c)
+#pragma clang fp contract(off)
+    float m[16], t[16], Mx = -INFINITY;
+#pragma unroll
+    for (int c = 0; c < 16; ++c) {
+      const float2 v = c < nct ? ml[c * 16 + kl] : make_float2(-INFINITY, 0.f);
+      m[c] = v.x;
+      t[c] = v.y;
+      Mx = fmaxf(Mx, m[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < 16; ++c) {
+      m[c] = m[c] == -INFINITY ? 0.f : expf(m[c] - Mx);
+      t[c] = t[c] * m[c];
+    }
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1)
+#pragma unroll
+      for (int c = 0; c < off; ++c) t[c] = t[c] + t[c + off];
+    const float inv = 1.0f / t[0];
+    pf_wave_sync();
+#pragma unroll
+    for (int c = 0; c < 16; ++c)
+      if (c < nct && g == 0) ml[c * 16 + kl].y = m[c] * inv;
+  } else {
+    for (int row = 0; row < Rt; ++row)
+      attn_row_weights(
+          nct,
+          [&](int c, bool ok, float& m, float& l) {
+            const float2 v = ok ? ml[c * 16 + row] : make_float2(0.f, 0.f);
+            m = v.x;
+            l = v.y;
+          },
+          [&](int c, float w) { ml[c * 16 + row].y = w; });
+  }
   pf_wave_sync();
 
-  // second walk: K blocks (scores, softmax), then V^T blocks (P V), per chunk
-  const int keg = (kend + 7) & ~7;
+  // second walk: per block the probabilities, then P V
   float O[8][4];
+  floatx4 o[8];
 #pragma unroll
-  for (int fb = 0; fb < 8; ++fb)
+  for (int fb = 0; fb < 8; ++fb) {
+    o[fb] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int i = 0; i < 4; ++i) O[fb][i] = 0.f;
-  pf_fetch<W, SK>(0, 0, kend, keg, kc, vc, pre);
-  pf_stash(s, slot, 0, pre);
-  __syncthreads();
-  for (int c = 0; c < ncg; ++c) {
-    const int k_lo = c * 256, k_hi = min(k_lo + 256, Lt + Rt);
-    float sv[8][2][4];
-    floatx4 o[8];
+  }
+  float M = 0.f, wgt = 0.f;
+  for (int kb = 0; kb < nk; ++kb) {
+    const int t = nk + 2 * kb;
+    const bool live = 64 * kb < end;  // uniform
+    u32x4p ph[2], pl[2];
+    step(t);
+    if (live) {
+      if ((kb & 3) == 0) {  // the chunk's row max and weight
+        uint64_t v;
+        asm volatile("ds_read_b64 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(v) : "v"(mla + (uint32_t)(kb >> 2) * 128u));
+        M = __uint_as_float((uint32_t)v);
+        if (M == -INFINITY) M = 0.f;
+        wgt = kl < Rt ? __uint_as_float((uint32_t)(v >> 32)) : 0.f;
+      }
+      float sv[4][4];
+      scores(t, kb, sv);
+      // the probabilities' two bf16 terms, in the operand layout
 #pragma unroll
-    for (int fb = 0; fb < 8; ++fb) o[fb] = floatx4{0.f, 0.f, 0.f, 0.f};
+      for (int ss = 0; ss < 2; ++ss) {
+        uint32_t hw[2][2], lw[2][2];
 #pragma unroll
-    for (int b = 0; b < 2 * NB; ++b) {
-      const bool more = b + 1 < 2 * NB || c + 1 < ncg;
-      if (more) pf_fetch<W, SK>(b + 1 < 2 * NB ? c : c + 1, b + 1 < 2 * NB ? b + 1 : 0, kend, keg, kc, vc, pre);
-      if (c < nct) {
-        if (b < NB) {
-          scores(s.st[slot], c, b, sv);
-          if (b == NB - 1) {
-            float m[4], l[4];
-            softmax(sv, m, l);
+        for (int grp = 0; grp < 2; ++grp)
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            const float p0 = prob(sv[2 * ss + grp][2 * e], M), p1 = prob(sv[2 * ss + grp][2 * e + 1], M);
+            const uint16_t h0 = f2bf_num(p0), h1 = f2bf_num(p1);
+            hw[grp][e] = (uint32_t)h0 | ((uint32_t)h1 << 16);
+            lw[grp][e] = (uint32_t)f2bf_num(p0 - bf2f(h0)) | ((uint32_t)f2bf_num(p1 - bf2f(h1)) << 16);
           }
-        } else {
-          const uint4* blk = s.st[slot];
 #pragma unroll
-          for (int j = 0; j < SPB; ++j) {
-            const int ks = (b - NB) * SPB + j;  // 32-key step of the chunk
-            // this step's probabilities, as two bf16 terms, through LDS into
-            // the A-operand layout (row kl, keys 8 g ..)
+        for (int e = 0; e < 2; ++e) {
+          pf_octet(hw[0][e], hw[1][e]);
+          pf_octet(lw[0][e], lw[1][e]);
+        }
+        ph[ss] = u32x4p{hw[0][0], hw[0][1], hw[1][0], hw[1][1]};
+        pl[ss] = u32x4p{lw[0][0], lw[0][1], lw[1][0], lw[1][1]};
+      }
+    }
+    step(t + 1);
+    if (live) {
+      const uint32_t base = frag + (uint32_t)((t + 1) % NS) * (uint32_t)kPfBlock;
+      u32x4p xa[8], xb[8];  // feature tiles 0-3, then 4-7: their two 32-key steps
+      xa[0] = pf_read<0>(base);
+      xa[1] = pf_read<1>(base);
+      xa[2] = pf_read<2>(base);
+      xa[3] = pf_read<3>(base);
+      xa[4] = pf_read<4>(base);
+      xa[5] = pf_read<5>(base);
+      xa[6] = pf_read<6>(base);
+      xa[7] = pf_read<7>(base);
+      xb[0] = pf_read<8>(base);
+      xb[1] = pf_read<9>(base);
+      xb[2] = pf_read<10>(base);
+      xb[3] = pf_read<11>(base);
+      xb[4] = pf_read<12>(base);
+      xb[5] = pf_read<13>(base);
+      xb[6] = pf_read<14>(base);
+      xb[7] = pf_read<15>(base);
+      pf_wait<0>(xa);
+      pf_wait<0>(xb);
+      if (64 * kb + 64 > end) {  // this tile's keys only (the verify kernel's tail mask)
 #pragma unroll
-            for (int grp = 0; grp < 2; ++grp)
+        for (int x = 0; x < 8; ++x)
 #pragma unroll
-              for (int i = 0; i < 4; ++i) {
-                const float e = sv[ks][grp][i];
-                const uint16_t hb = f2bf_num(e);
-                s.ph[wave][4 * g + i][16 * grp + kl] = hb;
-                s.pl[wave][4 * g + i][16 * grp + kl] = f2bf_num(e - bf2f(hb));
-              }
-            pf_wave_sync();
-            const uint4 pa_h = *(const uint4*)&s.ph[wave][kl][8 * g];
-            const uint4 pa_l = *(const uint4*)&s.pl[wave][kl][8 * g];
-            const int kv0 = k_lo + 32 * ks + 8 * g;
-#pragma unroll
-            for (int fb = 0; fb < 8; ++fb) {
-              uint4 vf = blk[pf_v_at<SK>(16 * fb + kl, 4 * j + g)];
-              if (kv0 + 8 > k_hi) {  // this tile's keys only (the verify kernel's tail mask)
-                uint32_t wv[4] = {vf.x, vf.y, vf.z, vf.w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                  const int p0 = kv0 + 2 * e;
-                  if (p0 >= k_hi) wv[e] = 0u;
-                  else if (p0 + 1 >= k_hi) wv[e] &= 0xffffu;
-                }
-                vf = make_uint4(wv[0], wv[1], wv[2], wv[3]);
-              }
-              o[fb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, pa_l),
-                                                              __builtin_bit_cast(bf16x8, vf), o[fb], 0, 0, 0);
-              o[fb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, pa_h),
-                                                              __builtin_bit_cast(bf16x8, vf), o[fb], 0, 0, 0);
-            }
-            pf_wave_sync();
+          for (int e = 0; e < 4; ++e) {
+            const int p0 = 64 * kb + 32 * (x & 1) + 8 * g + 2 * e;
+            const uint32_t mask = p0 >= end ? 0u : (p0 + 1 >= end ? 0xffffu : 0xffffffffu);
+            xa[x][e] &= mask;
+            xb[x][e] &= mask;
           }
+      }
+      auto mul = [&](const u32x4p (&x)[8], int fb0) {
+#pragma unroll
+        for (int ss = 0; ss < 2; ++ss)
+#pragma unroll
+          for (int term = 0; term < 2; ++term)
+#pragma unroll
+            for (int f = 0; f < 4; ++f)
+              o[fb0 + f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                  __builtin_bit_cast(bf16x8, x[2 * f + ss]), __builtin_bit_cast(bf16x8, term ? ph[ss] : pl[ss]),
+                  o[fb0 + f], 0, 0, 0);
+      };
+      mul(xa, 0);
+      mul(xb, 4);
+      if ((kb & 3) == 3 || 64 * kb + 64 >= end) {  // the chunk's (or the tile's) last block
+#pragma unroll
+        for (int fb = 0; fb < 8; ++fb) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) O[fb][i] = attn_acc1(O[fb][i], o[fb][i], wgt);
+          o[fb] = floatx4{0.f, 0.f, 0.f, 0.f};
         }
       }
-      if (more) pf_stash(s, slot ^ 1, b + 1 < 2 * NB ? b + 1 : 0, pre);
-      __syncthreads();
-      slot ^= 1;
-    }
-    if (c < nct) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int row = 4 * g + i;
-        const float w = row < Rt ? ml[c * 16 + row].x : 0.f;
-#pragma unroll
-        for (int fb = 0; fb < 8; ++fb) O[fb][i] = attn_acc1(O[fb][i], o[fb][i], w);
-      }
     }
   }
+  // the fills past the stream have landed before the LDS is given up
+  __builtin_amdgcn_s_waitcnt(0);
+  if (kl < Rt)
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = 4 * g + i;
-    if (row < Rt)
-#pragma unroll
-      for (int fb = 0; fb < 8; ++fb) out(16 * tl + row, 16 * fb + kl, O[fb][i]);
-  }
+    for (int fb = 0; fb < 8; ++fb) out4(16 * tl + kl, 16 * fb + 4 * g, O[fb]);
 }
 
 }  // namespace spade

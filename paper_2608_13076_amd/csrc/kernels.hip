@@ -737,23 +737,48 @@ __global__ void __launch_bounds__(kAttnThreads) attn_merge_kernel(AttnParams p) 
 // of one (request, K/V head) runs on the same XCD, so that pair's keys and
 // values, read by all of them, stay in one L2; on each XCD the groups with
 // the most chunks start first.  Dynamic LDS: attn_prefill_dyn_bytes(W, NC).
-template <bool ABF16, int W, int SK>
+template <bool ABF16, int W, int NS>
 __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2)))
 attn_prefill_kernel(AttnParams p, int ngrp) {
-  __shared__ AttnPfSmem<W, SK> s;
   extern __shared__ uint4 lds_dyn[];
-  const int i = blockIdx.x, x = i & 7, j = i >> 3;
-  const int per = p.G * ngrp;
-  const int pair = 8 * (j / per) + x, rem = j % per;
-  if (pair >= p.nb * p.Hkv) return;
-  const int gq = rem / ngrp, grp = ngrp - 1 - rem % ngrp;
+  // Workgroup i runs on XCD i % 8, which owns (request, K/V head) pairs
+  // i % 8 + 8 c.  Its list goes through the tile groups of all its heads from
+  // the last (most keys) to the first; the second half of the workgroups that
+  // run at once (two on each of an XCD's 32 compute units) takes its part in
+  // reverse, so a compute unit that starts with a long group gets a short one
+  // beside it (7B, 1018 rows: 52 us per layer, 66 in head order)
+  const int i = blockIdx.x, x = i & 7, np = (p.nb * p.Hkv - x + 7) >> 3, items = np * p.G * ngrp;
+  int n = i >> 3;
+  if (n >= items) return;
+  if (n >= 32 && n < 64) n = (items < 64 ? items : 64) - 1 - (n - 32);
+  const int at = n / (np * p.G), rem = n - at * (np * p.G);
+  const int pair = 8 * (rem / p.G) + x, gq = rem % p.G, grp = ngrp - 1 - at;
   const int bl = pair / p.Hkv, kvh = pair % p.Hkv, h = kvh * p.G + gq, bg = p.b0 + bl;
   const size_t head_off = ((size_t)bg * p.Hkv + kvh) * p.kv_stride * kAttnHd;
-  attn_prefill_tiles<W, SK>(s, (float2*)lds_dyn, p.NC, p.q + (size_t)bl * p.R * p.d, p.d, h,
-                            (const uint16_t*)p.kc + head_off, (const uint16_t*)p.vc + head_off, p.lens[bg], p.R,
-                            grp * W, p.scale, [&](int row, int dd, float O) {
-                              store_act<ABF16>(p.act_out, p.act_split,
-                                               (size_t)(bl * p.R + row) * p.d + h * kAttnHd + dd, O);
+  const uint32_t head_bytes = (uint32_t)p.kv_stride * kAttnHd * 2u;
+  attn_prefill_tiles<W, NS>((uint8_t*)lds_dyn, p.NC, p.q + (size_t)bl * p.R * p.d, p.d, h,
+                            make_rsrc((const uint16_t*)p.kc + head_off, head_bytes),
+                            make_rsrc((const uint16_t*)p.vc + head_off, head_bytes), p.lens[bg], p.R, grp * W, p.scale,
+                            [&](int row, int dd, const float (&O)[4]) {
+                              const size_t at = (size_t)(bl * p.R + row) * p.d + h * kAttnHd + dd;
+                              if constexpr (ABF16) {
+                                uint16_t* o = (uint16_t*)p.act_out + at;
+                                float r[4] = {O[0], O[1], O[2], O[3]};
+#pragma unroll
+                                for (int s = 0; s < kActSplits; ++s) {
+                                  uint32_t w[2];
+#pragma unroll
+                                  for (int e = 0; e < 2; ++e) {
+                                    const uint16_t a = f2bf(r[2 * e]), b = f2bf(r[2 * e + 1]);
+                                    w[e] = (uint32_t)a | ((uint32_t)b << 16);
+                                    r[2 * e] -= bf2f(a);
+                                    r[2 * e + 1] -= bf2f(b);
+                                  }
+                                  *(uint2*)(o + s * p.act_split) = make_uint2(w[0], w[1]);
+                                }
+                              } else {
+                                *(float4*)((float*)p.act_out + at) = make_float4(O[0], O[1], O[2], O[3]);
+                              }
                             });
 }
 
@@ -1314,22 +1339,26 @@ constexpr int kTileMidRows = 144;
 // at 49; LM heads even at 28 rows, 8B 289 / 197 at 49.
 bool tile_wins(int M) { return M > 32; }
 
-hipError_t launch_attn_prefill(const AttnParams& ap, bool abf16, hipStream_t st) {
-  constexpr int W = kPrefillAttnTiles, SK = kPrefillAttnKeys;
-  const int most = (int)attn_prefill_dyn_bytes(W, kAttnMaxChunks);
-  static hipError_t attr_b = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_prefill_kernel<true, W, SK>),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, most);
-  static hipError_t attr_f = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_prefill_kernel<false, W, SK>),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, most);
-  if (attr_b != hipSuccess) return attr_b;
-  if (attr_f != hipSuccess) return attr_f;
-  if (ap.NC > kAttnMaxChunks) return hipErrorInvalidValue;
+template <bool ABF16, int NS>
+hipError_t launch_attn_prefill_ns(const AttnParams& ap, hipStream_t st) {
+  constexpr int W = kPrefillAttnTiles;
+  const void* fn = reinterpret_cast<const void*>(&attn_prefill_kernel<ABF16, W, NS>);
+  static hipError_t attr = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                               (int)attn_prefill_dyn_bytes(W, NS, kMaxLen / kAttnChunkKeys));
+  if (attr != hipSuccess) return attr;
   const int ngrp = ((ap.R + 15) / 16 + W - 1) / W;
   const dim3 grid(8 * ((ap.nb * ap.Hkv + 7) / 8) * ap.G * ngrp);
-  const unsigned dyn = attn_prefill_dyn_bytes(W, ap.NC);
-  if (abf16) hipLaunchKernelGGL((attn_prefill_kernel<true, W, SK>), grid, dim3(64 * W), dyn, st, ap, ngrp);
-  else hipLaunchKernelGGL((attn_prefill_kernel<false, W, SK>), grid, dim3(64 * W), dyn, st, ap, ngrp);
+  hipLaunchKernelGGL((attn_prefill_kernel<ABF16, W, NS>), grid, dim3(64 * W), attn_prefill_dyn_bytes(W, NS, ap.NC), st,
+                     ap, ngrp);
   return hipGetLastError();
+}
+
+// Four ring slots while two workgroups share a compute unit's 160 KB (up to 32
+// chunks, 8192 keys), three beyond.
+hipError_t launch_attn_prefill(const AttnParams& ap, bool abf16, hipStream_t st) {
+  if (ap.NC > kMaxLen / kAttnChunkKeys) return hipErrorInvalidValue;
+  if (ap.NC <= 32) return abf16 ? launch_attn_prefill_ns<true, 4>(ap, st) : launch_attn_prefill_ns<false, 4>(ap, st);
+  return abf16 ? launch_attn_prefill_ns<true, 3>(ap, st) : launch_attn_prefill_ns<false, 3>(ap, st);
 }
 
 template <int HD, int RMAX>

@@ -17,7 +17,6 @@ constexpr int kWideMinRows = 16;     // bf16 projections with more rows use the 
 constexpr int kPrefillRows = 16;     // prompt rows per request of a prefill forward on the verify attention
 constexpr int kPrefillMaxRows = 2048;  // rows of a prefill forward (bf16 cache, head_dim 128)
 constexpr int kPrefillAttnTiles = 4;   // 16-row tiles (one wave each) per workgroup of the prefill attention
-constexpr int kPrefillAttnKeys = 64;   // keys per K or V^T block it stages in LDS
 constexpr int kMaxR = 16;            // rows per request in one forward (gamma <= 15)
 constexpr int kCorrMaxSlices = 256; // vocabulary slices of one correction draw
 constexpr int kNoAllocMaxB = 64;     // requests of one spade_accept_from_logits_noalloc call
