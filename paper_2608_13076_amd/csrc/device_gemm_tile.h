@@ -146,7 +146,7 @@ __device__ __forceinline__ void tile_epilogue(const GemmParams& a, int u, int ml
     const int pos = ok ? a.lens[bg] + ir : 0;
     const int pph = a.hd >> 4;
     int pw;
-    const int sec = qkv_section(u, a.d, a.Hkv * a.hd, &pw);
+    const int sec = qkv_section(a.unit0 + u, a.d, a.Hkv * a.hd, &pw);
     const int h = pw / pph, wg = pw - h * pph;  // query head (sec 0) or K/V head
     float o[16];
     if (sec < 2) {

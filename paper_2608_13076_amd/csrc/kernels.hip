@@ -1477,21 +1477,25 @@ hipError_t launch_layer_gemm(spade_model md, spade_kv kv, int kind, int layer, c
     int mode = M <= kTileMidRows ? md->mid_gemm : md->big_gemm;
     if (md->big_gemm == 2 || mode == 2) mode = lm ? 0 : 2;
     const bool wide_fixed = md->wide_rt > 0 || md->wide_p > 0 || md->wide_ks > 0;
-    if (mode != 1 && !(lm && md->wide_rt < 0) && (mode == 2 || !wide_fixed)) {
+    if (mode != 1 && !(lm && md->wide_rt < 0) && (mode == 2 || (!wide_fixed && (md->wide_rt < 0 || tile_wins(M))))) {
+      // the last layer of a prefill needs no query panels
+      if (kind == GEMM_QKV && fc.tokens != nullptr && !fc.want_logits && layer + 1 == D.L) {
+        g.unit0 = D.d / 16;
+        wmat += (size_t)g.unit0 * (K / KBd) * kTileBytes;
+        units -= g.unit0;
+      }
       const TileChoice c = tile_choice(kind, M, units, K / KBd, md->n_cu, M <= kTileMidRows ? md->mid_ks : 0,
                                        W.tile_floats);
-      if (mode == 2 || md->wide_rt < 0 || tile_wins(M)) {
-        GemmParams gp = g;
-        gp.w = wmat;
-        gp.NKB = K / KBd;
-        gp.n_units = units;
-        gp.M = M;
-        gp.m0 = 0;
-        gp.act = act;
-        gp.act_split = act_split;
-        gp.act_stride = K;
-        return launch_tile(kind, gp, c, W.tile_part, st);
-      }
+      GemmParams gp = g;
+      gp.w = wmat;
+      gp.NKB = K / KBd;
+      gp.n_units = units;
+      gp.M = M;
+      gp.m0 = 0;
+      gp.act = act;
+      gp.act_split = act_split;
+      gp.act_stride = K;
+      return launch_tile(kind, gp, c, W.tile_part, st);
     }
   }
   if (wb && M > kWideMinRows && md->wide_rt >= 0) {
@@ -1594,6 +1598,8 @@ hipError_t launch_forward(spade_model md, spade_kv kv, const ForwardCall& fc, hi
 
   for (int l = 0; l < D.L; ++l) {
     if ((e = launch_layer_gemm(md, kv, GEMM_QKV, l, fc, st)) != hipSuccess) return e;
+    // without logits only the last layer's K and V rows are used
+    if (!fc.want_logits && l + 1 == D.L) break;
     AttnParams ap{};
     ap.q = W.q;
     ap.kc = kv->k + (size_t)l * kv_layer * kv_elt;
