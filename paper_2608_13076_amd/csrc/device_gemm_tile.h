@@ -562,28 +562,33 @@ struct GemmTile {
 
   int slot;  // ring slot of the slice in use
 
-  // This thread's sums for the row scales of rows 32 i + tid / 16: partials
-  // tid % 16, + 16, ... in order, as gemm_row_rinv takes them.
+  // Row scales of rows 32 i + tid / 16: this thread takes partials tid % 16,
+  // + 16, ... of each row in order, as gemm_row_rinv does.  The first 256 of a
+  // row are requested before the ring and summed once the ring's loads are on
+  // their way.
   static constexpr int NR = (RT + 1) / 2;
-  __device__ __forceinline__ void row_sums(float (&ss)[NR]) const {
+  __device__ __forceinline__ void row_load(int q0, float (&v)[NR][16]) const {
     const Rsrc rs = make_rsrc(a.ssq_in + (size_t)a.m0 * a.n_ssq, (uint32_t)((size_t)a.M * a.n_ssq * 4));
 #pragma unroll
-    for (int i = 0; i < NR; ++i) ss[i] = 0.f;
-    for (int q0 = tid & 15; q0 < a.n_ssq; q0 += 256) {
-      float v[NR][16];
+    for (int i = 0; i < NR; ++i) {
+      const int r = 32 * i + (tid >> 4), row = row0 + r;
 #pragma unroll
-      for (int i = 0; i < NR; ++i) {
-        const int r = 32 * i + (tid >> 4), row = row0 + r;
-#pragma unroll
-        for (int f = 0; f < 16; ++f) {
-          const int q = q0 + f * 16;
-          v[i][f] = ld_f32<false>(rs, (r < RT * 16 && row < a.M && q < a.n_ssq) ? (uint32_t)(row * a.n_ssq + q) * 4u : kOob);
-        }
+      for (int f = 0; f < 16; ++f) {
+        const int q = q0 + (tid & 15) + f * 16;
+        v[i][f] = ld_f32<false>(rs, (r < RT * 16 && row < a.M && q < a.n_ssq) ? (uint32_t)(row * a.n_ssq + q) * 4u : kOob);
       }
+    }
+  }
+  __device__ __forceinline__ void row_sums(float (&v)[NR][16], float (&ss)[NR]) const {
+#pragma unroll
+    for (int i = 0; i < NR; ++i) ss[i] = 0.f;
+    for (int q0 = 0;; row_load(q0, v)) {
 #pragma unroll
       for (int i = 0; i < NR; ++i)
 #pragma unroll
         for (int f = 0; f < 16; ++f) ss[i] += v[i][f];
+      q0 += 256;
+      if (q0 >= a.n_ssq) break;
     }
   }
 
@@ -607,8 +612,8 @@ struct GemmTile {
     // the row scales' loads go first (they are older than the ring's, so they
     // are waited for alone) and are summed once the ring's are on their way
     constexpr bool RINV = KIND != GEMM_O && KIND != GEMM_DOWN && !SPLIT;
-    float ss[NR];
-    if constexpr (RINV) row_sums(ss);
+    float ss[NR], sv[NR][16];
+    if constexpr (RINV) row_load(0, sv);
     __builtin_amdgcn_sched_barrier(0);
     if (T > 0) {
       slot = 0;
@@ -627,6 +632,8 @@ struct GemmTile {
         }
         __builtin_amdgcn_sched_barrier(0);
       }
+      if constexpr (RINV) row_sums(sv, ss);
+      __builtin_amdgcn_sched_barrier(0);
       wait_vmcnt<(DP - 1) * NFB + (D - 1) * P>();
       __builtin_amdgcn_sched_barrier(0);
       __builtin_amdgcn_s_barrier();
