@@ -66,6 +66,8 @@ constexpr int tile_stage(int p) { return p * 16 * kTileRowPad; }     // floats o
 
 // slices of weights in the register ring (divides the 8 of a k-block)
 constexpr int kTileDepth = 4;
+// row tiles staged at once by the epilogue
+constexpr int tile_chunk(int rt, int p) { return rt * p > 12 ? (rt + 1) / 2 : rt; }
 
 template <int RT, int P>
 struct GemmTileSmem {
@@ -74,7 +76,7 @@ struct GemmTileSmem {
     // pieces of row r at piece p ^ (r / 2): the 16 rows of a fragment read
     // land on distinct banks
     uint8_t ring[kTileDepth / 2 + 2][kActSplits][RT][2048];
-    float stage[kTileWaves][RT][tile_stage(P)];
+    float stage[kTileWaves][tile_chunk(RT, P)][tile_stage(P)];
   };
   uint8_t pad[1024];  // target of the fill loads past a slot's blocks (never read)
   float rinv[RT * 16];
@@ -345,6 +347,10 @@ struct GemmTile {
   static constexpr int NFB = (4 * RT + kTileWaves - 1) / kTileWaves;  // 1 KB fill blocks per wave and slot
   static constexpr int NL = NFB + 2 * P;           // loads per wave and slot, with 2 P weight fragments
   static constexpr int PF = RT < 3 ? RT : 3;       // row tiles whose fragments are read ahead
+  // whether a range's partials join the totals after its last slice instead of
+  // among its MFMAs: two copies of that slice cost RT P > 12 tiles their
+  // registers (RT = 8, P = 2: 226 instead of 256 and 204 bytes of scratch)
+  static constexpr bool LATE = RT * P > 12;
   static constexpr int NX = 4;                     // fragment registers: row tiles in flight and in use
   static_assert(8 % D == 0 && (8 * RT) % NX == 0 && PF < NX, "rings indexed by the slice within its k-block");
   static_assert((DP - 1) * NFB + (D - 1) * P < 64, "vmcnt range");
@@ -553,14 +559,24 @@ struct GemmTile {
       } else {
         close_tile(RT - 1);
       }
-      do {
-        ++rnext;
-        bnd = (NKB * rnext) / kGemmWaves;
-      } while (bnd == (kb0 + (t >> 3)) + 1 && rnext < kGemmWaves);
+      next_range(kb0 + (t >> 3));
     }
   }
 
   int slot;  // ring slot of the slice in use
+
+  __device__ __forceinline__ void next_range(int kb) {
+    do {
+      ++rnext;
+      bnd = (NKB * rnext) / kGemmWaves;
+    } while (bnd == kb + 1 && rnext < kGemmWaves);
+  }
+
+  __device__ __forceinline__ void range_end(int kb) {
+#pragma unroll
+    for (int mt = 0; mt < RT; ++mt) close_tile(mt);
+    next_range(kb);
+  }
 
   // Row scales of rows 32 i + tid / 16: this thread takes partials tid % 16,
   // + 16, ... of each row in order, as gemm_row_rinv does.  The first 256 of a
@@ -603,9 +619,14 @@ struct GemmTile {
   __device__ __forceinline__ void kblock(int kb, std::integer_sequence<int, I...>) {
     const int t0 = (kb - kb0) * 8;
     (slice<I, false>(t0 + I, std::make_integer_sequence<int, RT>{}), ...);
-    lds_drain();
-    if (kb + 1 == bnd) slice<7, true>(t0 + 7, std::make_integer_sequence<int, RT>{});
-    else slice<7, false>(t0 + 7, std::make_integer_sequence<int, RT>{});
+    if constexpr (!LATE) lds_drain();
+    if constexpr (LATE) {
+      slice<7, false>(t0 + 7, std::make_integer_sequence<int, RT>{});
+      if (kb + 1 == bnd) range_end(kb);
+    } else {
+      if (kb + 1 == bnd) slice<7, true>(t0 + 7, std::make_integer_sequence<int, RT>{});
+      else slice<7, false>(t0 + 7, std::make_integer_sequence<int, RT>{});
+    }
   }
 
   __device__ __forceinline__ void run() {
@@ -669,7 +690,23 @@ struct GemmTile {
       }
       __syncthreads();
       bool nan_seen = false;
-      tile_store<KIND, RT, P>(a, &sm.stage[wave][0][0], tot, row0, u0, sm.rinv, lane, nan_seen);
+      constexpr int CH = tile_chunk(RT, P);
+      {
+        floatx4 t[CH][P];
+#pragma unroll
+        for (int mt = 0; mt < CH; ++mt)
+#pragma unroll
+          for (int p = 0; p < P; ++p) t[mt][p] = tot[mt][p];
+        tile_store<KIND, CH, P>(a, &sm.stage[wave][0][0], t, row0, u0, sm.rinv, lane, nan_seen);
+      }
+      if constexpr (CH < RT) {
+        floatx4 t[RT - CH][P];
+#pragma unroll
+        for (int mt = CH; mt < RT; ++mt)
+#pragma unroll
+          for (int p = 0; p < P; ++p) t[mt - CH][p] = tot[mt][p];
+        tile_store<KIND, RT - CH, P>(a, &sm.stage[wave][0][0], t, row0 + CH * 16, u0, sm.rinv + CH * 16, lane, nan_seen);
+      }
       if (KIND == GEMM_LM && nan_seen) flag_error(a.err, SPADE_DERR_NAN);
     }
   }

@@ -82,7 +82,9 @@ hipError_t launch_tile_kind(const GemmParams& gp, const TileChoice& c, float* pa
       case 3: return launch_tile_rp<KIND, 3, 2>(gp, c.ks, part, st);
       case 4: return launch_tile_rp<KIND, 4, 2>(gp, c.ks, part, st);
       case 5: return launch_tile_rp<KIND, 5, 2>(gp, c.ks, part, st);
-      default: return launch_tile_rp<KIND, 6, 2>(gp, c.ks, part, st);
+      case 6: return launch_tile_rp<KIND, 6, 2>(gp, c.ks, part, st);
+      case 8: return launch_tile_rp<KIND, 8, 2>(gp, c.ks, part, st);
+      default: return launch_tile_rp<KIND, 9, 2>(gp, c.ks, part, st);
     }
   }
   switch (c.rt) {
@@ -95,16 +97,16 @@ hipError_t launch_tile_kind(const GemmParams& gp, const TileChoice& c, float* pa
 }
 
 // The tiles that are built, each with the time one workgroup takes for a 32-k
-// slice (us).  Fitted, with the constants of tile_choice, to 300 launches of
+// slice (us).  Fitted, with the constants of tile_choice, to 490 launches of
 // the 7B and 8B projections at 144, 1019 and 2040 rows over every tile and
-// k-split (rms error 8%; the picks within 8% of the fastest of each shape,
-// but the 8B down projection at 144 rows: 54 us against 47).
+// k-split (rms error 9%; the picks within 5% of the fastest of each shape).
 struct TileCost {
   int rt, p;
   double slice_us;
 };
-constexpr TileCost kTileCosts[] = {{2, 2, 0.362}, {3, 2, 0.418}, {4, 2, 0.479}, {5, 2, 0.57},  {6, 2, 0.631},
-                                   {4, 1, 0.273}, {5, 1, 0.354}, {6, 1, 0.378}, {7, 1, 0.415}, {9, 1, 0.546}};
+constexpr TileCost kTileCosts[] = {{2, 2, 0.362}, {3, 2, 0.418}, {4, 2, 0.479}, {5, 2, 0.56},
+                                   {6, 2, 0.609}, {8, 2, 0.694}, {9, 2, 0.828}, {4, 1, 0.273},
+                                   {5, 1, 0.354}, {6, 1, 0.378}, {7, 1, 0.415}, {9, 1, 0.545}};
 
 }  // namespace
 
