@@ -25,21 +25,7 @@ constexpr int kAttnRows = 16;  // rows per request (gamma + 1 <= 16)
 constexpr int kAttnThreads = 512;
 
 template <int CK>
-struct AttnSmem {
-  static_assert(CK == 128 || CK == 256, "chunk of 128 or 256 keys");
-  // probabilities as two bf16 terms (the A operand of O = P V); rows padded by
-  // 16 bytes so the 16 rows of a fragment read start in different banks; 16-byte
-  // aligned, so each lane's fragment is one ds_read_b128 (with the alignment of
-  // uint16_t alone it becomes two ds_read2_b32, whose 64 lanes conflict)
-  alignas(16) uint16_t ph[kAttnRows][CK + 8];
-  alignas(16) uint16_t pl[kAttnRows][CK + 8];
-  float pm[kAttnRows][8], ps[kAttnRows][8];  // per-wave row max / row sum
-  float m[kAttnRows], l[kAttnRows];
-};
-
-template <int CK>
 struct AttnRegs {
-  uint4 kf[CK / 128][4];  // [16-key group][32-feature slice]: key k_lo + (CK/8) w + 16 grp + kl
   uint4 vf[CK / 32];      // [32-key step]: V^T row 16 w + kl, keys k_lo + 32 ks + 8 g .. + 8
 };
 
@@ -130,38 +116,68 @@ __device__ __forceinline__ void attn_stage_q(uint16_t (*sqh)[kAttnQPitch], uint1
   *(uint2*)&sql[row][f] = make_uint2(lw[0], lw[1]);
 }
 
-// Cross-lane moves within a row of 16 lanes (DPP): lane i reads lane i^1,
-// i^2, 7-i (within its half row) and 15-i; the four steps reduce the row.
-template <int CTRL>
-__device__ __forceinline__ float dpp_f32(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
+// lanes l, l ^ 16 (then ^ 32) combined in every lane
+__device__ __forceinline__ float attn_add16(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float attn_add32(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float attn_max4(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(t[0]), __uint_as_float(t[1]));
 }
 
-__device__ __forceinline__ float row16_max(float v) {
-  v = fmaxf(v, dpp_f32<0xB1>(v));   // quad_perm [1,0,3,2]
-  v = fmaxf(v, dpp_f32<0x4E>(v));   // quad_perm [2,3,0,1]
-  v = fmaxf(v, dpp_f32<0x141>(v));  // row_half_mirror
-  return fmaxf(v, dpp_f32<0x140>(v));  // row_mirror
+// Quads q (this lane's four keys 4 g ..) of two 16-key groups, one register
+// each, to octet order: lane group g gets keys 8 g .. + 3 in a, + 4 .. + 7 in
+// b of the 32 keys.
+__device__ __forceinline__ void attn_octet(uint32_t& a, uint32_t& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  const auto t = __builtin_amdgcn_permlane16_swap(r[0], r[1], false, false);
+  a = t[0];
+  b = t[1];
 }
 
-__device__ __forceinline__ float row16_sum(float v) {
-  v += dpp_f32<0xB1>(v);
-  v += dpp_f32<0x4E>(v);
-  v += dpp_f32<0x141>(v);
-  return v + dpp_f32<0x140>(v);
-}
-
-// One chunk of the verify attention: the K fragments come from attn_load_k,
-// the queries from LDS (sqh / sql, their bf16 terms staged by the caller with
-// attn_stage_q: row i, feature f at [i][f], rows past R zero), and the V^T
-// fragments are requested only after the score products, into the registers
-// the K fragments held, so a wave holds one of the two at a time.
+// One chunk of the verify attention for the NR rows of a workgroup, packed
+// into T 16-row tiles: one query head's R rows (T = 1), or, for a
+// grouped-query model, the G R rows of all query heads of a K/V head, so the
+// chunk's keys and values pass through the compute unit once (packed row pr =
+// gg R + i: query head gg of the group, request row i; rows past NR are
+// masked).  Every packed row goes through the same instructions in the same
+// order, so a row's partial does not depend on the packing.
 //
-// Chunk softmax: each lane holds the scores of rows 4g..4g+3 for its keys;
-// row maxima and sums reduce over the 16 lanes of a row (DPP) and then over
-// the eight waves (LDS, in wave order).  Probabilities (exp2 of the
-// log2(e)-scaled difference) go to LDS once, as two bf16 terms, and every
-// wave reads them as the A operand of O = P V.
+// The K fragments come from attn_load_k, the queries from LDS (sqh / sql,
+// their bf16 terms staged by the caller with attn_stage_q, rows past NR zero);
+// the V^T fragments are requested only after the score products, into the
+// registers the K fragments held, so a wave holds one of the two at a time.
+//
+// The products are transposed (S^T = K Q^T, each wave its 32 keys; O^T = V^T
+// P^T, each wave its 16 features): a lane holds one query's scores, so the row
+// maximum and sum reduce in-lane first (the adds of a butterfly over 16 keys),
+// then over two lane swaps and the eight waves (LDS, in wave order), and the
+// probabilities (exp2 of the log2(e)-scaled difference, as two bf16 terms)
+// reach the second product's layout by lane swaps and one 16-byte LDS write
+// per term.  With rows across registers, reduced over 16 lanes, and the
+// probabilities written two bytes at a time, the grouped chunks took 55 us per
+// layer (8B, 16 requests x 9 rows; now 51), one request at batch 1 11.1 (7B,
+// 1030 keys; now 10.9); the multi-head batch is bound by HBM (7B, 16 requests:
+// 105 us either way).
+//
+// o[t]: packed row 16 t + kl, features 16 wave + 4 g + i (i = 0..3).
+template <int CK, int T>
+struct AttnSmem {
+  // probabilities as two bf16 terms (the operand of O^T = V^T P^T); rows padded
+  // by 16 bytes so the 16 rows of a fragment read start in different banks
+  alignas(16) uint16_t ph[16 * T][CK + 8];
+  alignas(16) uint16_t pl[16 * T][CK + 8];
+  float pm[16 * T][8], ps[16 * T][8];  // per-wave row max / row sum
+  float m[16 * T], l[16 * T];
+};
+
 template <int CK>
 __device__ __forceinline__ void attn_load_k(const AttnItem& it, int wave, int lane, uint4 (&kf)[CK / 128][4]) {
   const int g = lane >> 4, kl = lane & 15;
@@ -177,151 +193,65 @@ __device__ __forceinline__ void attn_load_k(const AttnItem& it, int wave, int la
   }
 }
 
-// Scores of one chunk, scaled and masked: sv[grp][i] is row 4g + i and key
-// k_lo + (CK/8) wave + 16 grp + kl of the lane (-inf past k_hi or after the
-// row's position).
-template <int CK>
-__device__ __forceinline__ void attn_scores(const AttnItem& it, const uint4 (&kf)[CK / 128][4],
-                                            const uint16_t (*sqh)[kAttnQPitch], const uint16_t (*sql)[kAttnQPitch],
-                                            float scale, float (&sv)[CK / 128][4]) {
-  constexpr int NG = CK / 128;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int g = lane >> 4, kl = lane & 15;
+// Query head within the group (gg) and request row (rw) of packed rows
+// p0 + 16 t + i (t < T, i < NI), p0 + 16 t + i = gg R + rw: two divisions,
+// then steps (a division per row costs some twenty VALU instructions).
+template <int T, int NI>
+__device__ __forceinline__ void attn_grp_rows(int p0, int R, int (&gg)[T][NI], int (&rw)[T][NI]) {
+  const int sq = 16 / R, sr = 16 - sq * R;
+  int q = p0 / R, r = p0 - q * R;
 #pragma unroll
-  for (int grp = 0; grp < NG; ++grp) {
-    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int t = 0; t < T; ++t) {
+    int qi = q, ri = r;
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      const uint4 qh = *(const uint4*)&sqh[kl][32 * ks + 8 * g];
-      const uint4 ql = *(const uint4*)&sql[kl][32 * ks + 8 * g];
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ql),
-                                                    __builtin_bit_cast(bf16x8, kf[grp][ks]), acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, qh),
-                                                    __builtin_bit_cast(bf16x8, kf[grp][ks]), acc, 0, 0, 0);
+    for (int i = 0; i < NI; ++i) {
+      gg[t][i] = qi;
+      rw[t][i] = ri;
+      if (++ri == R) {
+        ri = 0;
+        ++qi;
+      }
     }
-    const int key = it.k_lo + (CK / 8) * wave + 16 * grp + kl;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int row = 4 * g + i;
-      sv[grp][i] = (key < it.k_hi && key <= it.L + row) ? acc[i] * scale : -INFINITY;
+    r += sr;
+    q += sq;
+    if (r >= R) {
+      r -= R;
+      ++q;
     }
   }
 }
 
-// V^T fragments of a chunk: 8-key granules below k_hi rounded up to 8 (zero
-// past them).  A chunk's keys lie in one V block, where the fragment of
-// (feature tile = wave, 32-key step) is 1 KB contiguous (v_cache_index).
-template <int CK>
-__device__ __forceinline__ void attn_load_v(const AttnItem& it, int wave, int lane, AttnRegs<CK>& r) {
-  static_assert(kVBlock % CK == 0, "a chunk within one V block");
-  const int g = lane >> 4, kl = lane & 15;
-  const int ke = (it.k_hi + 7) & ~7;
-  const uint16_t* vfr = it.vc + v_cache_index(16 * wave + kl, it.k_lo + 8 * g, kAttnHd);
-#pragma unroll
-  for (int ks = 0; ks < CK / 32; ++ks) {
-    const int kv0 = it.k_lo + 32 * ks + 8 * g;
-    r.vf[ks] = make_uint4(0, 0, 0, 0);
-    if (kv0 + 8 <= ke) r.vf[ks] = ld_stream_g128(vfr + ks * 512);
-  }
-}
-
-// Chunk softmax of the scores: probabilities to sm.ph / sm.pl, and the row
-// max and row sum of rows < R to sm.m / sm.l (read after a barrier).
-template <int CK>
-__device__ __forceinline__ void attn_softmax(const float (&sv)[CK / 128][4], int R, AttnSmem<CK>& sm) {
-  constexpr int NG = CK / 128;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int g = lane >> 4, kl = lane & 15;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    float mx = sv[0][i];
-#pragma unroll
-    for (int grp = 1; grp < NG; ++grp) mx = fmaxf(mx, sv[grp][i]);
-    mx = row16_max(mx);
-    if (kl == 0) sm.pm[4 * g + i][wave] = mx;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = 4 * g + i;
-    const float4 a = *(const float4*)&sm.pm[row][0];
-    const float4 b = *(const float4*)&sm.pm[row][4];
-    const float M = fmaxf(fmaxf(fmaxf(a.x, a.y), fmaxf(a.z, a.w)), fmaxf(fmaxf(b.x, b.y), fmaxf(b.z, b.w)));
-    float sum = 0.f;
-#pragma unroll
-    for (int grp = 0; grp < NG; ++grp) {
-      const float e = (M == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((sv[grp][i] - M) * 1.44269504088896341f);
-      sum += e;
-      const uint16_t h = f2bf_num(e);
-      const int kc = (CK / 8) * wave + 16 * grp + kl;
-      sm.ph[row][kc] = h;
-      sm.pl[row][kc] = f2bf_num(e - bf2f(h));
-    }
-    sum = row16_sum(sum);
-    if (kl == 0) sm.ps[row][wave] = sum;
-  }
-  __syncthreads();
-  if (tid < R) {
-    float l = 0.f, M = -INFINITY;
-#pragma unroll
-    for (int w = 0; w < 8; ++w) {
-      l += sm.ps[tid][w];
-      M = fmaxf(M, sm.pm[tid][w]);
-    }
-    sm.m[tid] = M;
-    sm.l[tid] = l;
-  }
-}
-
-// O = P V over the chunk (P from sm.ph / sm.pl, V^T fragments masked past
-// k_hi): row 4g + i, feature 16 wave + kl in o[i].
-template <int CK>
-__device__ __forceinline__ floatx4 attn_pv(const AttnSmem<CK>& sm, const AttnRegs<CK>& r) {
-  const int lane = threadIdx.x & 63;
-  const int g = lane >> 4, kl = lane & 15;
-  floatx4 o = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int ks = 0; ks < CK / 32; ++ks) {
-    const uint4 ph = *(const uint4*)&sm.ph[kl][32 * ks + 8 * g];
-    const uint4 pl = *(const uint4*)&sm.pl[kl][32 * ks + 8 * g];
-    o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, pl), __builtin_bit_cast(bf16x8, r.vf[ks]), o,
-                                                0, 0, 0);
-    o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ph), __builtin_bit_cast(bf16x8, r.vf[ks]), o,
-                                                0, 0, 0);
-  }
-  return o;
-}
-
-// The verify kernels' chunk: the helpers above written out in one body, the
-// same operations in the same order (composed of the helper calls, the
-// one-chunk kernel needs 80 VGPRs and spills six; written out, 76 and none).
-template <int CK>
-__device__ __forceinline__ floatx4 attn_chunk_lr(const AttnItem& it, const uint4 (&kf)[CK / 128][4],
-                                                 const uint16_t (*sqh)[kAttnQPitch],
-                                                 const uint16_t (*sql)[kAttnQPitch], int R, float scale,
-                                                 AttnSmem<CK>& sm) {
-  constexpr int NG = CK / 128;
+template <int CK, int T>
+__device__ __forceinline__ void attn_chunk(const AttnItem& it, const uint4 (&kf)[CK / 128][4],
+                                           const uint16_t (*sqh)[kAttnQPitch], const uint16_t (*sql)[kAttnQPitch],
+                                           int R, int NR, float scale, AttnSmem<CK, T>& sm, floatx4 (&o)[T]) {
+  static_assert(CK == 256, "32 keys per wave");
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int g = lane >> 4, kl = lane & 15;
   const int ke = (it.k_hi + 7) & ~7;
-  float sv[NG][4];
+  int gg[T][1], rw[T][1];  // request row of packed row 16 t + kl
+  if constexpr (T > 1) attn_grp_rows<T, 1>(kl, R, gg, rw);
+  else rw[0][0] = R == NR ? kl : kl % R;
+  float sv[T][2][4];  // key k_lo + 32 wave + 16 grp + 4 g + i
 #pragma unroll
-  for (int grp = 0; grp < NG; ++grp) {
-    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int t = 0; t < T; ++t) {
+    const bool ok = 16 * t + kl < NR;
+    const int last = min(it.k_hi - 1, it.L + rw[t][0]);  // the row's last key of the chunk
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      const uint4 qh = *(const uint4*)&sqh[kl][32 * ks + 8 * g];
-      const uint4 ql = *(const uint4*)&sql[kl][32 * ks + 8 * g];
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ql),
-                                                    __builtin_bit_cast(bf16x8, kf[grp][ks]), acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, qh),
-                                                    __builtin_bit_cast(bf16x8, kf[grp][ks]), acc, 0, 0, 0);
-    }
-    const int key = it.k_lo + (CK / 8) * wave + 16 * grp + kl;
+    for (int grp = 0; grp < 2; ++grp) {
+      floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int row = 4 * g + i;
-      sv[grp][i] = (key < it.k_hi && key <= it.L + row) ? acc[i] * scale : -INFINITY;
+      for (int ks = 0; ks < 4; ++ks) {
+        const uint4 qh = *(const uint4*)&sqh[16 * t + kl][32 * ks + 8 * g];
+        const uint4 ql = *(const uint4*)&sql[16 * t + kl][32 * ks + 8 * g];
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[grp][ks]),
+                                                      __builtin_bit_cast(bf16x8, ql), acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[grp][ks]),
+                                                      __builtin_bit_cast(bf16x8, qh), acc, 0, 0, 0);
+      }
+      const int key = it.k_lo + 32 * wave + 16 * grp + 4 * g;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sv[t][grp][i] = (ok && key + i <= last) ? acc[i] * scale : -INFINITY;
     }
   }
   // the V^T fragments, after the score products (the K registers are free);
@@ -338,35 +268,51 @@ __device__ __forceinline__ floatx4 attn_chunk_lr(const AttnItem& it, const uint4
   }
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    float mx = sv[0][i];
+  for (int t = 0; t < T; ++t) {
+    float mx = sv[t][0][0];
 #pragma unroll
-    for (int grp = 1; grp < NG; ++grp) mx = fmaxf(mx, sv[grp][i]);
-    mx = row16_max(mx);
-    if (kl == 0) sm.pm[4 * g + i][wave] = mx;
+    for (int grp = 0; grp < 2; ++grp)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) mx = fmaxf(mx, sv[t][grp][i]);
+    mx = attn_max4(mx);
+    if (g == 0) sm.pm[16 * t + kl][wave] = mx;
   }
   __syncthreads();
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = 4 * g + i;
+  for (int t = 0; t < T; ++t) {
+    const int row = 16 * t + kl;
     const float4 a = *(const float4*)&sm.pm[row][0];
     const float4 b = *(const float4*)&sm.pm[row][4];
     const float M = fmaxf(fmaxf(fmaxf(a.x, a.y), fmaxf(a.z, a.w)), fmaxf(fmaxf(b.x, b.y), fmaxf(b.z, b.w)));
-    float sum = 0.f;
+    float e[2][4];
+    uint32_t hw[2][2], lw[2][2];
 #pragma unroll
-    for (int grp = 0; grp < NG; ++grp) {
-      const float e = (M == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((sv[grp][i] - M) * 1.44269504088896341f);
-      sum += e;
-      const uint16_t h = f2bf_num(e);
-      const int kc = (CK / 8) * wave + 16 * grp + kl;
-      sm.ph[row][kc] = h;
-      sm.pl[row][kc] = f2bf_num(e - bf2f(h));
+    for (int grp = 0; grp < 2; ++grp) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        e[grp][i] = (M == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((sv[t][grp][i] - M) * 1.44269504088896341f);
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        const float p0 = e[grp][2 * x], p1 = e[grp][2 * x + 1];
+        const uint16_t h0 = f2bf_num(p0), h1 = f2bf_num(p1);
+        hw[grp][x] = (uint32_t)h0 | ((uint32_t)h1 << 16);
+        lw[grp][x] = (uint32_t)f2bf_num(p0 - bf2f(h0)) | ((uint32_t)f2bf_num(p1 - bf2f(h1)) << 16);
+      }
     }
-    sum = row16_sum(sum);
-    if (kl == 0) sm.ps[row][wave] = sum;
+    float sum = (e[0][0] + e[1][0]) + (e[0][1] + e[1][1]);
+    sum += (e[0][2] + e[1][2]) + (e[0][3] + e[1][3]);
+    sum = attn_add32(attn_add16(sum));
+    if (g == 0) sm.ps[row][wave] = sum;
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      attn_octet(hw[0][x], hw[1][x]);
+      attn_octet(lw[0][x], lw[1][x]);
+    }
+    *(uint4*)&sm.ph[row][32 * wave + 8 * g] = make_uint4(hw[0][0], hw[0][1], hw[1][0], hw[1][1]);
+    *(uint4*)&sm.pl[row][32 * wave + 8 * g] = make_uint4(lw[0][0], lw[0][1], lw[1][0], lw[1][1]);
   }
   __syncthreads();
-  if (tid < R) {
+  if (tid < NR) {
     float l = 0.f, M = -INFINITY;
 #pragma unroll
     for (int w = 0; w < 8; ++w) {
@@ -377,17 +323,20 @@ __device__ __forceinline__ floatx4 attn_chunk_lr(const AttnItem& it, const uint4
     sm.l[tid] = l;
   }
   attn_mask_tail(it, lane, r);
-  floatx4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int ks = 0; ks < CK / 32; ++ks) {
-    const uint4 ph = *(const uint4*)&sm.ph[kl][32 * ks + 8 * g];
-    const uint4 pl = *(const uint4*)&sm.pl[kl][32 * ks + 8 * g];
-    o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, pl), __builtin_bit_cast(bf16x8, r.vf[ks]), o,
-                                                0, 0, 0);
-    o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ph), __builtin_bit_cast(bf16x8, r.vf[ks]), o,
-                                                0, 0, 0);
+  for (int t = 0; t < T; ++t) {
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < CK / 32; ++ks) {
+      const uint4 ph = *(const uint4*)&sm.ph[16 * t + kl][32 * ks + 8 * g];
+      const uint4 pl = *(const uint4*)&sm.pl[16 * t + kl][32 * ks + 8 * g];
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, r.vf[ks]),
+                                                    __builtin_bit_cast(bf16x8, pl), acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, r.vf[ks]),
+                                                    __builtin_bit_cast(bf16x8, ph), acc, 0, 0, 0);
+    }
+    o[t] = acc;
   }
-  return o;
 }
 
 // Last-arrival merge of the chunks of one (request, head).
@@ -455,26 +404,34 @@ __device__ __forceinline__ void attn_merge_pair(Rsrc rpo, const AttnMergeSmem& m
 // resets the counter.  part_o / part_ml: [bh][NC][Rmax][kAttnHd] /
 // [bh][NC][Rmax][2].  All 512 threads call it; inactive items only
 // synchronise.
-// Store this chunk's partial (o: the chunk function's result; m / l from sa) with
-// write-through stores, without waiting for them.
-template <int CK>
-__device__ __forceinline__ void attn_publish(const AttnItem& it, floatx4 o, const AttnSmem<CK>& sa, float* part_o,
-                                             float* part_ml, int H, int NC, int Rmax, int R) {
+// Store the chunk's partials (o: attn_chunk's result; m / l from sa) with
+// write-through stores, without waiting for them: packed row pr of the rows of
+// query heads h0 .. (R rows each) goes to head h0 + pr / R, row pr % R.
+template <int CK, int T>
+__device__ __forceinline__ void attn_publish(const AttnItem& it, int h0, const floatx4 (&o)[T], const AttnSmem<CK, T>& sa,
+                                             float* part_o, float* part_ml, int H, int NC, int Rmax, int R, int NR) {
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int g = lane >> 4, kl = lane & 15;
-  const size_t bh = (size_t)it.bl * H + it.h;
-  if (it.active) {
-    float* po = part_o + ((bh * NC + it.c) * Rmax) * kAttnHd + 16 * wave + kl;
+  const size_t bh0 = (size_t)it.bl * H + h0;
+  const Rsrc rpo = wave_rsrc(part_o + bh0 * NC * Rmax * kAttnHd);
+  int gq[T][1], rw[T][1];
+  if constexpr (T > 1) attn_grp_rows<T, 1>(kl, R, gq, rw);
+  else {
+    gq[0][0] = R == NR ? 0 : kl / R;
+    rw[0][0] = kl - gq[0][0] * R;
+  }
+  typedef uint32_t u32x4a __attribute__((ext_vector_type(4)));
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int row = 4 * g + i;
-      if (row < R) __hip_atomic_store(po + row * kAttnHd, o[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    float* pml = part_ml + ((bh * NC + it.c) * Rmax) * 2;
-    if (tid < R) {
-      __hip_atomic_store(pml + tid * 2, sa.m[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(pml + tid * 2 + 1, sa.l[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+  for (int t = 0; t < T; ++t) {
+    const uint32_t off = (uint32_t)(((gq[t][0] * NC + it.c) * Rmax + rw[t][0]) * kAttnHd + 16 * wave + 4 * g) * 4u;
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4a, o[t]), rpo, (int)(16 * t + kl < NR ? off : kOob), 0,
+                                           kAuxCoh);
+  }
+  if (tid < NR) {
+    const int gg = tid / R, row = tid - gg * R;
+    float* pml = part_ml + (((bh0 + gg) * NC + it.c) * Rmax + row) * 2;
+    __hip_atomic_store(pml, sa.m[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(pml + 1, sa.l[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
@@ -601,189 +558,11 @@ __device__ __forceinline__ void attn_arrive_merge(const AttnItem& it, int n_mine
 // attn_publish and attn_arrive_merge for a workgroup that computed the one
 // chunk it.
 template <int CK, bool COH = true, class Out>
-__device__ __forceinline__ void attn_publish_merge(const AttnItem& it, floatx4 o, const AttnSmem<CK>& sa,
+__device__ __forceinline__ void attn_publish_merge(const AttnItem& it, const floatx4 (&o)[1], const AttnSmem<CK, 1>& sa,
                                                    AttnMergeSmem& ms, float* part_o, float* part_ml,
                                                    uint32_t* attn_cnt, int H, int NC, int Rmax, int R, Out&& out) {
-  attn_publish<CK>(it, o, sa, part_o, part_ml, H, NC, Rmax, R);
+  attn_publish<CK, 1>(it, it.h, o, sa, part_o, part_ml, H, NC, Rmax, R, R);
   attn_arrive_merge<COH>(it, it.active ? 1 : 0, ms, part_o, part_ml, attn_cnt, H, NC, Rmax, R, out);
-}
-
-// Grouped-query variant of attn_chunk_lr: one workgroup computes the chunk
-// for all G query heads of a K/V head, so the chunk's keys and values pass
-// through the compute unit once.  The G R rows are packed into T 16-row
-// tiles (packed row pr = gg R + i: query head gg of the group, request row
-// i; rows past G R are masked).  Every packed row goes through the same
-// instructions in the same order as its row in attn_chunk_lr, so its
-// partial is bit-identical.  sqh / sql: the packed query rows, staged by
-// the caller with attn_stage_q.  o[t]: rows 16 t + 4 g + i (i = 0..3), feature 16 wave + kl.
-template <int CK, int T>
-struct AttnSmemG {
-  alignas(16) uint16_t ph[16 * T][CK + 8];
-  alignas(16) uint16_t pl[16 * T][CK + 8];
-  float pm[16 * T][8], ps[16 * T][8];
-  float m[16 * T], l[16 * T];
-};
-
-// Query head within the group (gg) and request row (rw) of packed rows
-// p0 + 16 t + i (t < T, i < NI), p0 + 16 t + i = gg R + rw: two divisions,
-// then steps (a division per row costs some twenty VALU instructions).
-template <int T, int NI>
-__device__ __forceinline__ void attn_grp_rows(int p0, int R, int (&gg)[T][NI], int (&rw)[T][NI]) {
-  const int sq = 16 / R, sr = 16 - sq * R;
-  int q = p0 / R, r = p0 - q * R;
-#pragma unroll
-  for (int t = 0; t < T; ++t) {
-    int qi = q, ri = r;
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      gg[t][i] = qi;
-      rw[t][i] = ri;
-      if (++ri == R) {
-        ri = 0;
-        ++qi;
-      }
-    }
-    r += sr;
-    q += sq;
-    if (r >= R) {
-      r -= R;
-      ++q;
-    }
-  }
-}
-
-template <int CK, int T>
-__device__ __forceinline__ void attn_chunk_grp(const AttnItem& it, const uint4 (&kf)[CK / 128][4],
-                                               const uint16_t (*sqh)[kAttnQPitch],
-                                               const uint16_t (*sql)[kAttnQPitch], int R, int NR, float scale,
-                                               AttnSmemG<CK, T>& sm, floatx4 (&o)[T]) {
-  constexpr int NG = CK / 128;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int g = lane >> 4, kl = lane & 15;
-  const int ke = (it.k_hi + 7) & ~7;
-  int gg[T][4], rw[T][4];
-  attn_grp_rows<T, 4>(4 * g, R, gg, rw);
-  float sv[T][NG][4];
-#pragma unroll
-  for (int t = 0; t < T; ++t)
-#pragma unroll
-    for (int grp = 0; grp < NG; ++grp) {
-      floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        const uint4 qh = *(const uint4*)&sqh[16 * t + kl][32 * ks + 8 * g];
-        const uint4 ql = *(const uint4*)&sql[16 * t + kl][32 * ks + 8 * g];
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ql),
-                                                      __builtin_bit_cast(bf16x8, kf[grp][ks]), acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, qh),
-                                                      __builtin_bit_cast(bf16x8, kf[grp][ks]), acc, 0, 0, 0);
-      }
-      const int key = it.k_lo + (CK / 8) * wave + 16 * grp + kl;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int pr = 16 * t + 4 * g + i;
-        sv[t][grp][i] = (pr < NR && key < it.k_hi && key <= it.L + rw[t][i]) ? acc[i] * scale : -INFINITY;
-      }
-    }
-  __builtin_amdgcn_sched_barrier(0);
-  AttnRegs<CK> r;
-  const uint16_t* vfr = it.vc + v_cache_index(16 * wave + kl, it.k_lo + 8 * g, kAttnHd);
-#pragma unroll
-  for (int ks = 0; ks < CK / 32; ++ks) {
-    const int kv0 = it.k_lo + 32 * ks + 8 * g;
-    r.vf[ks] = make_uint4(0, 0, 0, 0);
-    if (kv0 + 8 <= ke) r.vf[ks] = ld_stream_g128(vfr + ks * 512);
-  }
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int t = 0; t < T; ++t)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float mx = sv[t][0][i];
-#pragma unroll
-      for (int grp = 1; grp < NG; ++grp) mx = fmaxf(mx, sv[t][grp][i]);
-      mx = row16_max(mx);
-      if (kl == 0) sm.pm[16 * t + 4 * g + i][wave] = mx;
-    }
-  __syncthreads();
-#pragma unroll
-  for (int t = 0; t < T; ++t)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int row = 16 * t + 4 * g + i;
-      const float4 a = *(const float4*)&sm.pm[row][0];
-      const float4 b = *(const float4*)&sm.pm[row][4];
-      const float M = fmaxf(fmaxf(fmaxf(a.x, a.y), fmaxf(a.z, a.w)), fmaxf(fmaxf(b.x, b.y), fmaxf(b.z, b.w)));
-      float sum = 0.f;
-#pragma unroll
-      for (int grp = 0; grp < NG; ++grp) {
-        const float e = (M == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((sv[t][grp][i] - M) * 1.44269504088896341f);
-        sum += e;
-        const uint16_t h = f2bf_num(e);
-        const int kc = (CK / 8) * wave + 16 * grp + kl;
-        sm.ph[row][kc] = h;
-        sm.pl[row][kc] = f2bf_num(e - bf2f(h));
-      }
-      sum = row16_sum(sum);
-      if (kl == 0) sm.ps[row][wave] = sum;
-    }
-  __syncthreads();
-  if (tid < NR) {
-    float l = 0.f, M = -INFINITY;
-#pragma unroll
-    for (int w = 0; w < 8; ++w) {
-      l += sm.ps[tid][w];
-      M = fmaxf(M, sm.pm[tid][w]);
-    }
-    sm.m[tid] = M;
-    sm.l[tid] = l;
-  }
-  attn_mask_tail(it, lane, r);
-#pragma unroll
-  for (int t = 0; t < T; ++t) {
-    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int ks = 0; ks < CK / 32; ++ks) {
-      const uint4 ph = *(const uint4*)&sm.ph[16 * t + kl][32 * ks + 8 * g];
-      const uint4 pl = *(const uint4*)&sm.pl[16 * t + kl][32 * ks + 8 * g];
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, pl),
-                                                    __builtin_bit_cast(bf16x8, r.vf[ks]), acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ph),
-                                                    __builtin_bit_cast(bf16x8, r.vf[ks]), acc, 0, 0, 0);
-    }
-    o[t] = acc;
-  }
-}
-
-// Store the grouped chunk's partials where attn_publish stores each head's:
-// packed row pr goes to query head kvh G + pr / R, row pr % R.
-template <int CK, int T>
-__device__ __forceinline__ void attn_publish_grp(const AttnItem& it, int kvh, int G, const floatx4 (&o)[T],
-                                                 const AttnSmemG<CK, T>& sa, float* part_o, float* part_ml, int H,
-                                                 int NC, int Rmax, int R) {
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int g = lane >> 4, kl = lane & 15;
-  const int NR = G * R;
-  int gq[T][4], rw[T][4];
-  attn_grp_rows<T, 4>(4 * g, R, gq, rw);
-#pragma unroll
-  for (int t = 0; t < T; ++t)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int pr = 16 * t + 4 * g + i;
-      if (pr < NR) {
-        const size_t bh = (size_t)it.bl * H + kvh * G + gq[t][i];
-        float* po = part_o + ((bh * NC + it.c) * Rmax + rw[t][i]) * kAttnHd + 16 * wave + kl;
-        __hip_atomic_store(po, o[t][i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-    }
-  if (tid < NR) {
-    const int gg = tid / R, row = tid - gg * R;
-    const size_t bh = (size_t)it.bl * H + kvh * G + gg;
-    float* pml = part_ml + ((bh * NC + it.c) * Rmax + row) * 2;
-    __hip_atomic_store(pml, sa.m[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(pml + 1, sa.l[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -814,7 +593,7 @@ __device__ __forceinline__ void attn_publish_grp(const AttnItem& it, int kvh, in
 // The products are computed transposed (S^T = K Q^T, O^T = V^T P^T: the same
 // products summed over the same k order, so the same bits): a lane then holds
 // one query's column, the row maximum and sum are mostly in-lane (the adds of
-// row16_sum's butterfly, two of the four steps across lanes), and the
+// the verify kernel's butterfly, two of the four steps across lanes), and the
 // probabilities reach the second product's operand layout by two lane swaps
 // per register instead of through LDS.
 //
@@ -861,32 +640,6 @@ __device__ __forceinline__ void pf_wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// lanes l, l ^ 16 (then ^ 32) combined in every lane
-__device__ __forceinline__ float pf_add16(float v) {
-  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-__device__ __forceinline__ float pf_add32(float v) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-__device__ __forceinline__ float pf_max4(float v) {
-  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-  const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return fmaxf(__uint_as_float(t[0]), __uint_as_float(t[1]));
-}
-
-// Quads q (this lane's four keys 4 g ..) of two 16-key groups, one register
-// each, to octet order: lane group g gets keys 8 g .. + 3 in a, + 4 .. + 7 in
-// b of the 32 keys.
-__device__ __forceinline__ void pf_octet(uint32_t& a, uint32_t& b) {
-  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
-  const auto t = __builtin_amdgcn_permlane16_swap(r[0], r[1], false, false);
-  a = t[0];
-  b = t[1];
 }
 
 // q: this request's query rows ([R][d], head h's features at h * kAttnHd);
@@ -1061,26 +814,27 @@ __device__ __forceinline__ void attn_prefill_tiles(uint8_t* lds, int NCP, const 
       }
     }
     if (256 * c < end) {
-      float M = -INFINITY;
+      float M = sv[0][0][0];  // (NaN only if every score is)
 #pragma unroll
       for (int b = 0; b < 4; ++b)
 #pragma unroll
         for (int u = 0; u < 4; ++u)
 #pragma unroll
           for (int i = 0; i < 4; ++i) M = fmaxf(M, sv[b][u][i]);
-      M = pf_max4(M);
+      M = attn_max4(M);
       const float Mz = M == -INFINITY ? 0.f : M;  // an empty chunk: every probability exp2(-inf) = 0
       float lsum = 0.f;
 #pragma unroll
-      for (int vw = 0; vw < 8; ++vw) {  // 32-key slices, each in row16_sum's order
+      for (int vw = 0; vw < 8; ++vw) {  // 32-key slices, each in the verify kernel's order
         float e[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i)
           e[i] = prob(sv[vw >> 1][2 * (vw & 1)][i], Mz) + prob(sv[vw >> 1][2 * (vw & 1) + 1][i], Mz);
-        lsum += pf_add32(pf_add16((e[0] + e[1]) + (e[2] + e[3])));
+        lsum += attn_add32(attn_add16((e[0] + e[1]) + (e[2] + e[3])));
       }
+      if (M == -INFINITY) lsum = 0.f;
       if (g == 0) {
-        const uint64_t v = (uint64_t)__float_as_uint(M) | ((uint64_t)__float_as_uint(lsum) << 32);
+        const uint64_t v = (uint64_t)__float_as_uint(fmaxf(-INFINITY, M)) | ((uint64_t)__float_as_uint(lsum) << 32);
         asm volatile("ds_write_b64 %0, %1" ::"v"(mla + (uint32_t)c * 128u), "v"(v) : "memory");
       }
     }
@@ -1168,8 +922,8 @@ __device__ __forceinline__ void attn_prefill_tiles(uint8_t* lds, int NCP, const 
           }
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
-          pf_octet(hw[0][e], hw[1][e]);
-          pf_octet(lw[0][e], lw[1][e]);
+          attn_octet(hw[0][e], hw[1][e]);
+          attn_octet(lw[0][e], lw[1][e]);
         }
         ph[ss] = u32x4p{hw[0][0], hw[0][1], hw[1][0], hw[1][1]};
         pl[ss] = u32x4p{lw[0][0], lw[0][1], lw[1][0], lw[1][1]};

@@ -435,8 +435,7 @@ __global__ void __launch_bounds__(256) attn_kernel(AttnParams p) {
         const int k = kw + 4 * s2 + kg;
 #pragma unroll
         for (int e = 0; e < DPL; e += 4) {
-          float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-          if (k < k_hi) v = *(const float4*)(kc + kbase + (size_t)k * HD + dg * DPL + e);
+          const float4 v = *(const float4*)(kc + kbase + (size_t)k * HD + dg * DPL + e);
           kr[s2][e] = v.x;
           kr[s2][e + 1] = v.y;
           kr[s2][e + 2] = v.z;
@@ -640,12 +639,12 @@ inline int attn_grid(int n_runs, int Hkv, int G, int nb) { return 8 * G * ((n_ru
 // request's last key exit at once, and the last chunk of a (request, head) to
 // finish merges them into the O-projection operand.  The queries are staged in
 // LDS and the V^T fragments loaded after the score products into the
-// registers K held (attn_chunk_lr): 78 VGPRs, three workgroups per compute
+// registers K held (attn_chunk): 78 VGPRs, three workgroups per compute
 // unit (keeping K, V and the queries in registers at once took 120: two).
 template <bool ABF16, int CK, bool ARRIVE>
 __global__ void __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(6)))
 attn_lr_kernel(AttnParams p) {
-  __shared__ AttnSmem<CK> sm;
+  __shared__ AttnSmem<CK, 1> sm;
   __shared__ AttnMergeSmem ms;
   __shared__ alignas(16) uint16_t sqh[kAttnRows][kAttnQPitch];
   __shared__ alignas(16) uint16_t sql[kAttnRows][kAttnQPitch];
@@ -664,9 +663,10 @@ attn_lr_kernel(AttnParams p) {
   attn_load_k<CK>(it, wave, lane, kf);
   attn_stage_q(sqh, sql, qrow, 4 * f4, qv);
   __syncthreads();
-  const floatx4 o = attn_chunk_lr<CK>(it, kf, sqh, sql, p.R, p.scale, sm);
+  floatx4 o[1];
+  attn_chunk<CK, 1>(it, kf, sqh, sql, p.R, p.R, p.scale, sm, o);
   if constexpr (!ARRIVE) {  // attn_merge_kernel merges after this launch
-    attn_publish<CK>(it, o, sm, p.part_o, p.part_ml, p.H, p.NC, p.Rmax, p.R);
+    attn_publish<CK, 1>(it, h, o, sm, p.part_o, p.part_ml, p.H, p.NC, p.Rmax, p.R, p.R);
     return;
   }
   attn_publish_merge<CK, false>(it, o, sm, ms, p.part_o, p.part_ml, p.cnt, p.H, p.NC, p.Rmax, p.R, [&](int oi, float O) {
@@ -676,13 +676,13 @@ attn_lr_kernel(AttnParams p) {
 }
 
 // Grouped-query chunks: one workgroup per (chunk, K/V head, request) for all
-// G query heads of the K/V head (attn_chunk_grp, T 16-row tiles of packed
+// G query heads of the K/V head (attn_chunk, T 16-row tiles of packed
 // rows); the partials are merged by attn_merge_kernel.
 template <bool ABF16, int T>
 __global__ void __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(4)))
 attn_g_kernel(AttnParams p) {
   constexpr int CK = kAttnChunkKeys;
-  __shared__ AttnSmemG<CK, T> sm;
+  __shared__ AttnSmem<CK, T> sm;
   __shared__ alignas(16) uint16_t sqh[16 * T][kAttnQPitch];
   __shared__ alignas(16) uint16_t sql[16 * T][kAttnQPitch];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -711,8 +711,8 @@ attn_g_kernel(AttnParams p) {
   for (int j = 0; j < T; ++j) attn_stage_q(sqh, sql, (tid >> 5) + 16 * j, 4 * f4, qv[j]);
   __syncthreads();
   floatx4 o[T];
-  attn_chunk_grp<CK, T>(it, kf, sqh, sql, p.R, NR, p.scale, sm, o);
-  attn_publish_grp<CK, T>(it, kvh, p.G, o, sm, p.part_o, p.part_ml, p.H, p.NC, p.Rmax, p.R);
+  attn_chunk<CK, T>(it, kf, sqh, sql, p.R, NR, p.scale, sm, o);
+  attn_publish<CK, T>(it, kvh * p.G, o, sm, p.part_o, p.part_ml, p.H, p.NC, p.Rmax, p.R, NR);
 }
 
 // Second pass of the attention for launches with several rounds of chunk
