@@ -370,14 +370,30 @@ __device__ __forceinline__ void correct_slice(const AcceptParams& p, int b, int 
   const int per = (V + S - 1) / S;
   const int v0 = s * per, v1 = min(V, v0 + per);
   Best br{-INFINITY, 0x7fffffff}, bp{-INFINITY, 0x7fffffff};
-#pragma unroll 4
-  for (int v = v0 + tid; v < v1; v += NT) {
-    const float lv = row[v], g = gumbel_at(seed, v);
-    const float sc = corr_score_p(lv, invT, g);
-    if (sc == sc) bp = better(bp, Best{sc, v});
-    if (residual) {
-      const float sr = corr_score_res(lv, invT, lse, qrow[v], g);
-      if (sr == sr) br = better(br, Best{sr, v});
+  // four tokens per thread and step: their logits and q requested first, the
+  // noise (which needs neither) computed while they travel.  No load
+  // is under a branch.
+  // (16 rows of a 128K vocabulary: a loop of single loads took 23.0 us, this 19.8)
+  const uint32_t bytes = (uint32_t)(v1 - v0) * 4u;
+  const Rsrc rl = make_rsrc(row + v0, bytes), rq = make_rsrc(residual ? qrow + v0 : row, residual ? bytes : 0u);
+  for (int base = v0; base < v1; base += 4 * NT) {
+    float lv[4], qv[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t off = (uint32_t)(base - v0 + j * NT + tid) * 4u;  // past the slice: past the resource
+      lv[j] = ld_f32<false>(rl, off);
+      qv[j] = ld_f32<false>(rq, off);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int v = base + j * NT + tid;
+      const float g = gumbel_at(seed, v);
+      const float sc = corr_score_p(lv[j], invT, g);
+      if (v < v1 && sc == sc) bp = better(bp, Best{sc, v});
+      if (residual) {
+        const float sr = corr_score_res(lv[j], invT, lse, qv[j], g);
+        if (v < v1 && sr == sr) br = better(br, Best{sr, v});
+      }
     }
   }
   br = wave_best(br);
