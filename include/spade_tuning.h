@@ -21,7 +21,9 @@ extern "C" {
 
 /* Tiling of the batched projections.  A verify call with more than 16 rows
  * (B * (gamma + 1) > 16) and bf16 weights runs the QKV, O, gate/up and down
- * projections on the wide-row GEMM: each weight tile is read once per launch
+ * projections on the wide-row GEMM up to 32 rows, and with more where the
+ * tiled GEMM is off (spade_model_set_mid_gemm, spade_model_set_big_gemm) or
+ * this call fixes a tiling: each weight tile is read once per launch
  * and multiplied with `row_tiles` 16-row tiles of the activations held in
  * LDS; each wave owns `panels` 16-column weight panels, so that every
  * activation fragment read from LDS feeds that many matrix instructions.  The
@@ -85,8 +87,7 @@ spade_status spade_model_set_attn_grouped(spade_model m, int mode);
 spade_status spade_model_set_prefill_rows(spade_model m, int rows);
 
 /* Tiled GEMM of forwards of more than 144 rows (prefill; bf16 weights): a
- * workgroup of eight waves owns up to 96 rows and 256 columns, or up to 144
- * rows and 128 columns, the activations pass through an LDS ring filled by
+ * workgroup of eight waves owns up to 144 rows and 256 columns, the activations pass through an LDS ring filled by
  * direct loads and the weights go straight into registers.  mode 0 (the
  * default) uses it for every launch; mode 1 turns it off (the wide-row GEMM
  * runs instead); mode 2 uses it for every projection launch of more than 16

@@ -64,7 +64,7 @@ struct GemmParams {
   int V;
   float* stats;  // [M][NU][3]: (max, sum exp, argmax) of z = logit (/T) per row and workgroup
   int NU;        // workgroups of the LM-head launch
-  float* pstats; // [M][n_units][3]: the same per row and panel (wide-row and split-K LM heads)
+  float* pstats; // [M][n_units][3]: the same per row and panel (tiled, wide-row and split-K LM heads)
   const uint8_t* mode;
   float inv_T;
   int have_q;

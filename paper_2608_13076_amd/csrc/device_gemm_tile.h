@@ -11,7 +11,7 @@
 // P = 2 the L2 path (26 KB per slice at RT = 5; without the MFMAs the 7B
 // gate/up launch of 144 rows takes 72 of its 81 us, without the loads 56), at
 // P = 1 the LDS reads.  Few rows and long weights: RT = 9, P = 1 covers 144
-// rows with one row group; prefill: RT = 4 or 6, P = 2.  Four waves of twice
+// rows with one row group; prefill: RT = 6 to 9, P = 2.  Four waves of twice
 // the panels (one per SIMD, 512 registers) halve the LDS reads and measured
 // 5-10% slower: a lone wave's MFMAs wait behind its own loads.
 //

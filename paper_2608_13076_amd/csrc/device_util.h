@@ -57,8 +57,8 @@ __device__ __forceinline__ uint4 ld_b128(Rsrc r, uint32_t off) {
 // about 6.1 TB/s without (one to four 8-wave workgroups per CU, plain and
 // direct-to-LDS buffer loads alike).  The weight tiles of the verify-call
 // GEMMs are loaded with it (each is read by one workgroup, or by the few row
-// groups of a wide-row launch, once per call); the big prefill GEMM, whose
-// tiles many row-tile workgroups re-read through L2, runs slower with it.
+// groups of a wide-row or tiled launch, once per call); prefill launches, whose
+// tiles many row groups re-read through L2, run slower with it.
 constexpr int kAuxStream = 2;
 
 __device__ __forceinline__ uint4 ld_stream_b128(Rsrc r, uint32_t off) {

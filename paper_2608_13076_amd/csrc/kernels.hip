@@ -21,8 +21,8 @@
 //                  and panels per workgroup, the operand through an LDS ring,
 //                  optional k-splits for the O and down projections
 //   gemm_tile_kernel   (gemm_tile.hip) launches of more than 32 rows: batched
-//                  verification and prefill forwards, up to 96 rows x 256 or
-//                  144 rows x 128 columns per workgroup; k-split launches
+//                  verification and prefill forwards, up to 144 rows x 256
+//                  columns per workgroup; k-split launches
 //                  publish sums that gemm_tile_finish_kernel adds
 //   attn_lr_kernel the bf16 / head_dim-128 verify attention, one 256-key
 //                  chunk per workgroup; merges the chunks of a (request,
@@ -1138,7 +1138,7 @@ int split_k_choice(const GemmParams& gp, int n_cu, int fixed) {
 }  // namespace
 
 // Whether the LM head of a call with M rows leaves one statistics entry per
-// row and panel (wide-row or split-K engine; the accept step then folds the
+// row and panel (tiled, wide-row or split-K engine; the accept step then folds the
 // panels in the skinny engine's workgroup order): the number of panels, else
 // 0 (one entry per workgroup).  The same conditions as launch_layer_gemm.
 int lm_stats_panels(spade_model md, int M) {
@@ -1455,7 +1455,7 @@ hipError_t launch_layer_gemm(spade_model md, spade_kv kv, int kind, int layer, c
       g.ssq_in = W.ssq;
       g.logits = fc.logits_out;
       g.stats = W.stats;
-      g.pstats = W.stats;  // per-panel layout when the wide-row or split-K engine runs it
+      g.pstats = W.stats;  // per-panel layout when the tiled, wide-row or split-K engine runs it
       g.mode = fc.mode;
       g.inv_T = fc.inv_T;
       g.have_q = fc.have_q;
@@ -1464,9 +1464,9 @@ hipError_t launch_layer_gemm(spade_model md, spade_kv kv, int kind, int layer, c
   const int grid = std::min(units, md->gemm_wgs);
   g.NU = grid;  // LM head: one statistics entry per workgroup and row
   if (wb && M > kWideMinRows) {
-    // more than 16 rows: the tiled GEMM where its estimate beats the wide-row
-    // GEMM's measured range (tile_wins), unless a setting turns it off or
-    // fixes the other engine's schedule; the LM head only where the accept
+    // the tiled GEMM where it measured faster than the wide-row one
+    // (tile_wins), unless a setting turns it off or fixes the other engine's
+    // schedule; the LM head only where the accept
     // step expects per-panel statistics
     const bool lm = kind == GEMM_LM;
     int mode = M <= kTileMidRows ? md->mid_gemm : md->big_gemm;
@@ -1900,8 +1900,8 @@ namespace {
 
 // Prompt rows of one prefill forward, per request and in all.  A bf16 cache
 // with head_dim 128 takes up to the workspace's rows (the prefill attention
-// covers any number of rows per request; the projections then run on the
-// wide-row GEMM, every weight tile read once per launch for all rows); other
+// covers any number of rows per request; the projections run on the tiled
+// GEMM); other
 // caches take kPrefillRows per request (the verify attention's limit).  A
 // model setting can lower the rows per request.
 void prefill_caps(spade_model md, int* r_cap, int* m_cap) {

@@ -13,7 +13,7 @@ namespace spade {
 constexpr int kPanel = 16;           // weight rows per MFMA tile (one panel)
 constexpr int kTileBytes = 8192;     // one panel x one k-block, in the arena
 constexpr int kMaxRowsPerGemm = 32;  // rows handled by one skinny-GEMM launch
-constexpr int kWideMinRows = 16;     // bf16 projections with more rows use the wide-row GEMM
+constexpr int kWideMinRows = 16;     // bf16 projections with more rows use the wide-row or the tiled GEMM
 constexpr int kPrefillRows = 16;     // prompt rows per request of a prefill forward on the verify attention
 constexpr int kPrefillMaxRows = 2048;  // rows of a prefill forward (bf16 cache, head_dim 128)
 constexpr int kPrefillAttnTiles = 4;   // 16-row tiles (one wave each) per workgroup of the prefill attention

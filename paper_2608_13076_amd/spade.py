@@ -209,15 +209,14 @@ class Model:
         _check(self.lib.spade_model_set_prefill_rows(self.handle, int(rows)))
 
     def set_big_gemm(self, mode: int) -> None:
-        """Projection GEMM of forwards with many rows: 0 where it fills the
-        chip, 1 off, 2 for every launch of more than 16 rows (not the LM head)."""
+        """Tiled GEMM of forwards of more than 144 rows: 0 on, 1 off, 2 for
+        every projection launch of more than 16 rows (not the LM head)."""
         _check(self.lib.spade_model_set_big_gemm(self.handle, int(mode)))
 
     def set_mid_gemm(self, mode: int, k_splits: int = 0) -> None:
-        """Projection GEMM of batched calls of up to 144 rows: mode 0 gate/up
-        from 113 rows, O from 129, down from 137, 1 off, 2 every projection
-        from 17 rows (not the LM head); k_splits 0 chosen per launch, 1..8
-        fixed."""
+        """Tiled GEMM of batched calls of up to 144 rows: mode 0 from 33 rows,
+        1 off, 2 every projection from 17 rows (not the LM head); k_splits 0
+        chosen per launch, 1..8 fixed."""
         _check(self.lib.spade_model_set_mid_gemm(self.handle, int(mode), int(k_splits)))
 
     def set_correction_slices(self, mode: int) -> None:
