@@ -101,7 +101,8 @@ ArenaLayout layout_of(const Dims& D) {
 
 struct WsPlan {
   size_t x, act_n, act_o, act_f, ssq, q, attn_o, attn_ml, attn_cnt, logits, stats, rope, err, split_cnt,
-      split_part, wide_cnt, wide_part, tile_part, corr_lse, corr_part, corr_cnt, prefill_tok, prefill_cnt, prefill_base, total;
+      split_part, wide_cnt, wide_part, tile_part, corr_lse, corr_part, corr_cnt, prefill_tok, prefill_cnt, prefill_base,
+      prefill_map, prefill_off, total;
   size_t wide_items, wide_floats, tile_floats;
   int max_units;
   size_t act_split, actf_split;
@@ -169,6 +170,8 @@ WsPlan plan_ws(const Dims& D, int max_batch, int max_gamma, int max_len) {
   p.prefill_tok = take((size_t)p.Mrows * 4);
   p.prefill_cnt = take((size_t)max_batch * 4);
   p.prefill_base = take((size_t)max_batch * 4);
+  p.prefill_map = take((size_t)p.Mrows * 4);
+  p.prefill_off = take((kPrefillPack + 1) * 4);
   p.total = off;
   return p;
 }
@@ -265,6 +268,8 @@ spade_status spade_model_create(const spade_config* cfg, void* d_weights, void* 
   w.prefill_tok = (int32_t*)(b + p.prefill_tok);
   w.prefill_cnt = (int32_t*)(b + p.prefill_cnt);
   w.prefill_base = (int32_t*)(b + p.prefill_base);
+  w.prefill_map = (int32_t*)(b + p.prefill_map);
+  w.prefill_off = (int32_t*)(b + p.prefill_off);
   w.logits = (float*)(b + p.logits);
   w.stats = (float*)(b + p.stats);
   w.rope = (float*)(b + p.rope);

@@ -46,6 +46,7 @@ struct GemmParams {
   void* vc;
   uint32_t kv_bytes;  // bytes of one layer's K (or V) cache
   int H, hd, d, kv_stride, kv_bf16;
+  const int32_t* row_map;  // packed prefill (tiled GEMM): request << 16 | row of each row, or NULL
   int unit0;  // panel of the QKV matrix that the launch's first panel is (tiled GEMM)
   int Hkv;  // K/V heads (the cache's head count; H for multi-head attention)
   const float* rope;

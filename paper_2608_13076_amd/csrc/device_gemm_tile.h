@@ -145,7 +145,13 @@ __device__ __forceinline__ void tile_epilogue(const GemmParams& a, int u, int ml
                                               bool& nan_seen) {
   if constexpr (KIND == GEMM_QKV) {
     const int m = a.m0 + ml;
-    const int bl = m / a.R, ir = m - bl * a.R, bg = a.b0 + bl;
+    int bl = m / a.R, ir = m - bl * a.R;
+    if (a.row_map != nullptr) {
+      const int rm = ok ? a.row_map[m] : 0;
+      bl = rm >> 16;
+      ir = rm & 0xffff;
+    }
+    const int bg = a.b0 + bl;
     const int pos = ok ? a.lens[bg] + ir : 0;
     const int pph = a.hd >> 4;
     int pw;

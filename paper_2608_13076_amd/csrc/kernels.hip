@@ -95,21 +95,28 @@ struct EmbedParams {
   uint32_t* err;
   int32_t* lens;   // global [Bmax] cached lengths
   int len_limit;   // lens[b] + R may not exceed this (cache capacity, attention coverage)
+  const int32_t* row_map;  // packed prefill, or NULL
+  const int32_t* row_off;
 };
 
 template <bool WBF16>
 __global__ void __launch_bounds__(256) embed_kernel(EmbedParams p) {
   const int m = blockIdx.x;
-  const int bl = m / p.R, i = m % p.R;
+  int bl = m / p.R, i = m % p.R, R = p.R;
+  if (p.row_map != nullptr) {
+    bl = p.row_map[m] >> 16;
+    i = p.row_map[m] & 0xffff;
+    R = p.row_off[bl + 1] - p.row_off[bl];
+  }
   // A length the host could not bound (lens written outside the library's
   // calls): clamp it so every later kernel of the call stays inside the cache
   // and the attention's chunk grid, and flag the call.  The later kernels run
   // after this one on the same stream.
   if (i == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
     const int L = p.lens[p.b0 + bl];
-    if (L < 0 || L > p.len_limit - p.R) {
+    if (L < 0 || L > p.len_limit - R) {
       flag_error(p.err, SPADE_DERR_CAPACITY);
-      p.lens[p.b0 + bl] = L < 0 ? 0 : p.len_limit - p.R;
+      p.lens[p.b0 + bl] = L < 0 ? 0 : p.len_limit - R;
     }
   }
   int t;
@@ -201,6 +208,7 @@ struct AttnParams {
   int b0, R, H, d, kv_stride;
   int Hkv, G;  // K/V heads of the cache; query head h reads K/V head h / G
   int CK, NC;
+  const int32_t* row_off;  // packed prefill: first row of each request (and the end), or NULL: R rows each
   int nb;  // requests of the call (bf16 kernels: the grid is one-dimensional)
   float scale;
   float* part_o;
@@ -749,13 +757,19 @@ attn_prefill_kernel(AttnParams p, int ngrp) {
   const int at = n / (np * p.G), rem = n - at * (np * p.G);
   const int pair = 8 * (rem / p.G) + x, gq = rem % p.G, grp = ngrp - 1 - at;
   const int bl = pair / p.Hkv, kvh = pair % p.Hkv, h = kvh * p.G + gq, bg = p.b0 + bl;
+  int row0 = bl * p.R, R = p.R;
+  if (p.row_off != nullptr) {
+    row0 = p.row_off[bl];
+    R = p.row_off[bl + 1] - row0;
+    if (grp * W * 16 >= R) return;  // a shorter request than the longest: no such group
+  }
   const size_t head_off = ((size_t)bg * p.Hkv + kvh) * p.kv_stride * kAttnHd;
   const uint32_t head_bytes = (uint32_t)p.kv_stride * kAttnHd * 2u;
-  attn_prefill_tiles<W, NS>((uint8_t*)lds_dyn, p.NC, p.q + (size_t)bl * p.R * p.d, p.d, h,
+  attn_prefill_tiles<W, NS>((uint8_t*)lds_dyn, p.NC, p.q + (size_t)row0 * p.d, p.d, h,
                             make_rsrc((const uint16_t*)p.kc + head_off, head_bytes),
-                            make_rsrc((const uint16_t*)p.vc + head_off, head_bytes), p.lens[bg], p.R, grp * W, p.scale,
+                            make_rsrc((const uint16_t*)p.vc + head_off, head_bytes), p.lens[bg], R, grp * W, p.scale,
                             [&](int row, int dd, const float (&O)[4]) {
-                              const size_t at = (size_t)(bl * p.R + row) * p.d + h * kAttnHd + dd;
+                              const size_t at = (size_t)(row0 + row) * p.d + h * kAttnHd + dd;
                               if constexpr (ABF16) {
                                 uint16_t* o = (uint16_t*)p.act_out + at;
                                 float r[4] = {O[0], O[1], O[2], O[3]};
@@ -992,7 +1006,7 @@ __global__ void advance_kernel(int b, int count, int32_t* lens, int32_t* pending
 // written past its length); each length then advances by its real tokens;
 // last, the pending tokens.
 struct PrefillCounts {
-  int n[64];
+  int n[kPrefillPack];
 };
 
 __global__ void prefill_counts_kernel(PrefillCounts c, int b0, int nb, int32_t* dst, const int32_t* lens,
@@ -1012,13 +1026,37 @@ __global__ void prefill_gather_kernel(const int32_t* tokens, int ld, const int32
   out[m] = (pos >= 0 && pos < n_cache[b]) ? tokens[(size_t)b * ld + pos] : 0;
 }
 
-__global__ void prefill_advance_kernel(int b0, int nb, int R, const int32_t* n_cache, const int32_t* base,
-                                       int32_t* lens) {
+// A packed forward: request b0 + i of nb has c.n[i] rows (none, for requests
+// with no tokens left), one after the other.  Token, request and row of every
+// packed row, and each request's first row.
+__global__ void prefill_pack_kernel(PrefillCounts c, const int32_t* tokens, int ld, const int32_t* n_cache,
+                                    const int32_t* base, const int32_t* lens, int b0, int nb, int32_t* out,
+                                    int32_t* map, int32_t* off) {
+  const int m = blockIdx.x * blockDim.x + threadIdx.x;
+  int bl = 0, first = 0, total = 0, before = 0;
+  for (int i = 0; i < nb; ++i) {
+    if (m >= total) {
+      bl = i;
+      first = total;
+    }
+    total += c.n[i];
+    if (i < m) before += c.n[i];
+  }
+  if (m <= nb) off[m] = before;
+  if (m >= total) return;
+  const int b = b0 + bl, pos = lens[b] - base[b] + (m - first);
+  out[m] = (pos >= 0 && pos < n_cache[b]) ? tokens[(size_t)b * ld + pos] : 0;
+  map[m] = bl << 16 | (m - first);
+}
+
+__global__ void prefill_advance_kernel(int b0, int nb, int R, const int32_t* off, const int32_t* n_cache,
+                                       const int32_t* base, int32_t* lens) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < nb) {
     const int b = b0 + i;
     const int rem = n_cache[b] - (lens[b] - base[b]);
-    lens[b] += rem <= 0 ? 0 : (rem < R ? rem : R);
+    const int rows = off != nullptr ? off[i + 1] - off[i] : R;
+    lens[b] += rem <= 0 ? 0 : (rem < rows ? rem : rows);
   }
 }
 
@@ -1334,6 +1372,19 @@ constexpr int kTileMidRows = 144;
 // at 49; LM heads even at 28 rows, 8B 289 / 197 at 49.
 bool tile_wins(int M) { return M > 32; }
 
+// Whether a launch of M rows runs on the tiled GEMM: where it measured faster
+// than the wide-row one, unless a setting turns it off or fixes the other
+// engine's schedule; the LM head only where the accept step expects per-panel
+// statistics.
+bool runs_tiled(spade_model md, int kind, int M) {
+  if (md->dims.wdt != SPADE_BF16 || M <= kWideMinRows) return false;
+  const bool lm = kind == GEMM_LM;
+  int mode = M <= kTileMidRows ? md->mid_gemm : md->big_gemm;
+  if (md->big_gemm == 2 || mode == 2) mode = lm ? 0 : 2;
+  const bool wide_fixed = md->wide_rt > 0 || md->wide_p > 0 || md->wide_ks > 0;
+  return mode != 1 && !(lm && md->wide_rt < 0) && (mode == 2 || (!wide_fixed && (md->wide_rt < 0 || tile_wins(M))));
+}
+
 template <bool ABF16, int NS>
 hipError_t launch_attn_prefill_ns(const AttnParams& ap, hipStream_t st) {
   constexpr int W = kPrefillAttnTiles;
@@ -1388,10 +1439,11 @@ hipError_t launch_layer_gemm(spade_model md, spade_kv kv, int kind, int layer, c
   const size_t kv_layer = (size_t)kv->max_batch * D.KVH * kv->stride * D.hd;  // elements
   const size_t kv_elt = D.kvdt == SPADE_BF16 ? 2 : 4;
   const uint8_t* lb = md->weights + (size_t)layer * md->lay.layer_bytes;
-  const int M = fc.nb * fc.R;
+  const int M = fc.rows > 0 ? fc.rows : fc.nb * fc.R;
 
   GemmParams g{};
   g.R = fc.R;
+  g.row_map = fc.row_map;
   g.b0 = fc.b0;
   g.lens = kv->lens;
   g.inv_din = 1.0f / (float)D.d;
@@ -1463,35 +1515,26 @@ hipError_t launch_layer_gemm(spade_model md, spade_kv kv, int kind, int layer, c
   }
   const int grid = std::min(units, md->gemm_wgs);
   g.NU = grid;  // LM head: one statistics entry per workgroup and row
-  if (wb && M > kWideMinRows) {
-    // the tiled GEMM where it measured faster than the wide-row one
-    // (tile_wins), unless a setting turns it off or fixes the other engine's
-    // schedule; the LM head only where the accept
-    // step expects per-panel statistics
-    const bool lm = kind == GEMM_LM;
-    int mode = M <= kTileMidRows ? md->mid_gemm : md->big_gemm;
-    if (md->big_gemm == 2 || mode == 2) mode = lm ? 0 : 2;
-    const bool wide_fixed = md->wide_rt > 0 || md->wide_p > 0 || md->wide_ks > 0;
-    if (mode != 1 && !(lm && md->wide_rt < 0) && (mode == 2 || (!wide_fixed && (md->wide_rt < 0 || tile_wins(M))))) {
-      // the last layer of a prefill needs no query panels
-      if (kind == GEMM_QKV && fc.tokens != nullptr && !fc.want_logits && layer + 1 == D.L) {
-        g.unit0 = D.d / 16;
-        wmat += (size_t)g.unit0 * (K / KBd) * kTileBytes;
-        units -= g.unit0;
-      }
-      const TileChoice c = tile_choice(kind, M, units, K / KBd, md->n_cu, M <= kTileMidRows ? md->mid_ks : 0,
-                                       W.tile_floats);
-      GemmParams gp = g;
-      gp.w = wmat;
-      gp.NKB = K / KBd;
-      gp.n_units = units;
-      gp.M = M;
-      gp.m0 = 0;
-      gp.act = act;
-      gp.act_split = act_split;
-      gp.act_stride = K;
-      return launch_tile(kind, gp, c, W.tile_part, st);
+  if (kind == GEMM_QKV && fc.row_map != nullptr && !runs_tiled(md, kind, M)) return hipErrorInvalidValue;
+  if (runs_tiled(md, kind, M)) {
+    // the last layer of a prefill needs no query panels
+    if (kind == GEMM_QKV && fc.tokens != nullptr && !fc.want_logits && layer + 1 == D.L) {
+      g.unit0 = D.d / 16;
+      wmat += (size_t)g.unit0 * (K / KBd) * kTileBytes;
+      units -= g.unit0;
     }
+    const TileChoice c = tile_choice(kind, M, units, K / KBd, md->n_cu, M <= kTileMidRows ? md->mid_ks : 0,
+                                     W.tile_floats);
+    GemmParams gp = g;
+    gp.w = wmat;
+    gp.NKB = K / KBd;
+    gp.n_units = units;
+    gp.M = M;
+    gp.m0 = 0;
+    gp.act = act;
+    gp.act_split = act_split;
+    gp.act_stride = K;
+    return launch_tile(kind, gp, c, W.tile_part, st);
   }
   if (wb && M > kWideMinRows && md->wide_rt >= 0) {
     // batched rows: every row in one launch, weights streamed once
@@ -1536,7 +1579,7 @@ hipError_t launch_forward(spade_model md, spade_kv kv, const ForwardCall& fc, hi
   const Dims& D = md->dims;
   const Workspace& W = md->ws;
   const bool wb = D.wdt == SPADE_BF16;
-  const int M = fc.nb * fc.R;
+  const int M = fc.rows > 0 ? fc.rows : fc.nb * fc.R;
   hipError_t e;
 
   EmbedParams ep{};
@@ -1555,6 +1598,8 @@ hipError_t launch_forward(spade_model md, spade_kv kv, const ForwardCall& fc, hi
   ep.ssq = W.ssq;
   ep.err = W.err;
   ep.lens = kv->lens;
+  ep.row_map = fc.row_map;
+  ep.row_off = fc.row_off;
 
   const size_t kv_layer = (size_t)kv->max_batch * D.KVH * kv->stride * D.hd;  // elements
   const size_t kv_elt = D.kvdt == SPADE_BF16 ? 2 : 4;
@@ -1562,7 +1607,8 @@ hipError_t launch_forward(spade_model md, spade_kv kv, const ForwardCall& fc, hi
   // attention chunks over the longest request: for a bf16 cache with
   // head_dim 128 the 8-wave MFMA kernel, else kAttnChunk
   int max_keys = 0;
-  for (int b = fc.b0; b < fc.b0 + fc.nb; ++b) max_keys = std::max(max_keys, kv->lens_ub[b] + fc.R);
+  for (int b = fc.b0; b < fc.b0 + fc.nb; ++b) 
+    max_keys = std::max(max_keys, kv->lens_ub[b] + (fc.counts != nullptr ? fc.counts[b - fc.b0] : fc.R));
   const bool tiled = D.kvdt == SPADE_BF16 && D.hd == kAttnHd;
   const bool mfma_attn = tiled && fc.R <= kAttnRows;
   // more rows per request than one verify call: the prefill attention
@@ -1619,6 +1665,7 @@ hipError_t launch_forward(spade_model md, spade_kv kv, const ForwardCall& fc, hi
     const dim3 agrid(NC, D.H, fc.nb);
     const bool kvb = D.kvdt == SPADE_BF16;
     ap.nb = fc.nb;
+    ap.row_off = fc.row_off;
     if (prefill_attn) {
       e = launch_attn_prefill(ap, wb, st);
     } else if (mfma_attn && two_pass) {
@@ -1915,8 +1962,13 @@ void prefill_caps(spade_model md, int* r_cap, int* m_cap) {
 
 }  // namespace
 
-// Requests go through in index order, in ranges [b0, b0 + nb) with R rows
-// each: a range starts at the first request with tokens left (R = its
+// Requests go through in index order, in ranges [b0, b0 + nb).  Where the
+// tiled GEMM and the prefill attention run (they take any row's request from
+// a table), a forward's rows are the real tokens of its requests one after the
+// other, up to the caps: no row is a placeholder, and long prompts fill every
+// forward but the last (five prompts of 59-155 tokens on an 8B shape, 4
+// layers, first token included: 2.22 ms; with R rows each, 2.88).  Otherwise (few
+// rows, other caches or engines) each request of a range has R rows: a range starts at the first request with tokens left (R = its
 // remaining tokens, up to the caps) and takes in the next requests while all
 // nb R rows fit the workspace, every request of the range has R free
 // positions in the cache, and at least half the rows are real tokens.  Rows
@@ -1940,9 +1992,21 @@ hipError_t launch_prefill_batch(spade_model md, spade_kv kv, int B, const int32_
   while (e == hipSuccess) {
     while (b0 < B && rem[b0] == 0) ++b0;
     if (b0 == B) break;
-    int R = std::min(rem[b0], r_cap), nb = 1;
+    PrefillCounts pc{};
+    int rows = 0, nb = 0, R = 0;
+    for (int b = b0; b < B && nb < kPrefillPack && rows < m_cap; ++b, ++nb) {
+      pc.n[nb] = std::min(std::min(rem[b], std::min(r_cap, 0xffff)), m_cap - rows);
+      rows += pc.n[nb];
+      R = std::max(R, pc.n[nb]);
+    }
+    const bool packed = md->dims.kvdt == SPADE_BF16 && md->dims.hd == kAttnHd && R > kAttnRows &&
+                        runs_tiled(md, GEMM_QKV, rows);
+    if (!packed) {
+      R = std::min(rem[b0], r_cap);
+      nb = 1;
+    }
     int top = kv->lens_ub[b0];  // the longest cached length of the range
-    while (b0 + nb < B) {
+    while (!packed && b0 + nb < B) {
       const int c = b0 + nb;
       const int R2 = std::max(R, std::min(rem[c], r_cap));
       const int top2 = std::max(top, kv->lens_ub[c]);
@@ -1954,9 +2018,19 @@ hipError_t launch_prefill_batch(spade_model md, spade_kv kv, int B, const int32_
       top = top2;
       ++nb;
     }
-    hipLaunchKernelGGL(prefill_gather_kernel, dim3((nb * R + 255) / 256), dim3(256), 0, st, tokens, ld,
-                       W.prefill_cnt, W.prefill_base, kv->lens, b0, nb, R, W.prefill_tok);
     ForwardCall fc{};
+    if (packed) {
+      hipLaunchKernelGGL(prefill_pack_kernel, dim3((std::max(rows, nb + 1) + 255) / 256), dim3(256), 0, st, pc, tokens,
+                         ld, W.prefill_cnt, W.prefill_base, kv->lens, b0, nb, W.prefill_tok, W.prefill_map,
+                         W.prefill_off);
+      fc.rows = rows;
+      fc.counts = pc.n;
+      fc.row_map = W.prefill_map;
+      fc.row_off = W.prefill_off;
+    } else {
+      hipLaunchKernelGGL(prefill_gather_kernel, dim3((nb * R + 255) / 256), dim3(256), 0, st, tokens, ld,
+                         W.prefill_cnt, W.prefill_base, kv->lens, b0, nb, R, W.prefill_tok);
+    }
     fc.b0 = b0;
     fc.nb = nb;
     fc.R = R;
@@ -1964,14 +2038,14 @@ hipError_t launch_prefill_batch(spade_model md, spade_kv kv, int B, const int32_
     fc.want_logits = false;
     e = launch_forward(md, kv, fc, st);
     if (e == hipSuccess) {
-      hipLaunchKernelGGL(prefill_advance_kernel, dim3((nb + 63) / 64), dim3(64), 0, st, b0, nb, R, W.prefill_cnt,
-                         W.prefill_base, kv->lens);
+      hipLaunchKernelGGL(prefill_advance_kernel, dim3((nb + 63) / 64), dim3(64), 0, st, b0, nb, R, fc.row_off,
+                         W.prefill_cnt, W.prefill_base, kv->lens);
       e = hipGetLastError();
     }
     // the host bound of lens follows the device lengths (the next forward
     // sizes its attention grid from it)
     for (int b = b0; b < b0 + nb; ++b) {
-      const int t = std::min(rem[b], R);
+      const int t = packed ? pc.n[b - b0] : std::min(rem[b], R);
       rem[b] -= t;
       kv->lens_ub[b] += t;
     }

@@ -16,6 +16,7 @@ constexpr int kMaxRowsPerGemm = 32;  // rows handled by one skinny-GEMM launch
 constexpr int kWideMinRows = 16;     // bf16 projections with more rows use the wide-row or the tiled GEMM
 constexpr int kPrefillRows = 16;     // prompt rows per request of a prefill forward on the verify attention
 constexpr int kPrefillMaxRows = 2048;  // rows of a prefill forward (bf16 cache, head_dim 128)
+constexpr int kPrefillPack = 64;      // requests of a packed prefill forward
 constexpr int kPrefillAttnTiles = 4;   // 16-row tiles (one wave each) per workgroup of the prefill attention
 constexpr int kMaxR = 16;            // rows per request in one forward (gamma <= 15)
 constexpr int kCorrMaxSlices = 256; // vocabulary slices of one correction draw
@@ -138,6 +139,8 @@ struct Workspace {
   uint32_t* corr_cnt;   // [Bmax] arrival counters of the correction slices (kept at zero between calls)
   int32_t* prefill_tok; // [Mrows] token ids of one batched-prefill forward
   int32_t* prefill_cnt; // [Bmax] prompt tokens to cache per request (batched prefill)
+  int32_t* prefill_map; // [Mrows] rows of a packed prefill forward: request of the range << 16 | row of the request
+  int32_t* prefill_off; // [kPrefillPack + 1] first packed row of each request of the range
   int32_t* prefill_base; // [Bmax] each request's length when its batched prefill began
   size_t act_split;   // elements between splits of act_n / act_o
   size_t actf_split;  // elements between splits of act_f
@@ -190,7 +193,11 @@ struct spade_kv_s {
 namespace spade {
 
 struct ForwardCall {
-  int b0, nb, R;           // requests [b0, b0+nb), R rows each
+  int b0, nb, R;           // requests [b0, b0+nb), R rows each (packed: at most R)
+  int rows;                // packed prefill: rows in all; 0: nb R
+  const int* counts;       // packed prefill (host): rows of each request
+  const int32_t* row_map;  // packed prefill: Workspace.prefill_map, prefill_off
+  const int32_t* row_off;
   const int32_t* tokens;   // prefill: [R] ids; verify: NULL
   const int32_t* drafts;   // verify: [nb][R-1]
   bool want_logits;
