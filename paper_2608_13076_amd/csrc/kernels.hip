@@ -1000,8 +1000,8 @@ __global__ void advance_kernel(int b, int count, int32_t* lens, int32_t* pending
   }
 }
 
-// Batched prefill.  A forward takes the next R prompt tokens of requests
-// [b0, b0 + nb), each from the offset it has reached (its length now minus
+// Batched prefill.  A forward takes the next R prompt tokens (packed: c.n[i],
+// prefill_pack_kernel) of requests [b0, b0 + nb), each from the offset it has reached (its length now minus
 // its length when the prefill began; 0 past its end: a placeholder row,
 // written past its length); each length then advances by its real tokens;
 // last, the pending tokens.
