@@ -246,7 +246,7 @@ spade_status spade_prefill_batch(spade_model m, spade_kv kv, int B, const int32_
 
 /* Probabilities softmax(logits / temperature) of `rows` rows of V logits,
  * float32, row-major [rows][V] in and out (device pointers, caller-owned; out
- * may not alias in).  The edge side of Algorithm 1 keeps, for every draft
+ * may be in itself, else must not overlap it).  The edge side of Algorithm 1 keeps, for every draft
  * token, the distribution q it was drawn from (Sec. III-C: the acceptance
  * test and the residual need q); with the draft model run through
  * spade_verify with gamma = 0, this turns that call's logits into q.

@@ -1916,10 +1916,13 @@ hipError_t launch_pack(spade_model md, int kind, int layer, const void* src, hip
 
 hipError_t launch_softmax(const float* logits, int rows, int V, float invT, float* out, hipStream_t st) {
   // slices from two of them on (every slice then holds more than 1000
-  // tokens); shorter rows, and more rows than a grid's y dimension, in one
-  // workgroup each
+  // tokens); shorter rows, more rows than a grid's y dimension and in-place
+  // calls (the slices' scratch lies in the output before the last read of the
+  // logits) in one workgroup each
   const int S = std::min(kSoftmaxMaxSlices, (V + kSoftmaxSlice - 1) / kSoftmaxSlice);
-  if (S < 2 || rows > 65535) {
+  const uintptr_t n = (uintptr_t)rows * V * 4, in = (uintptr_t)logits, to = (uintptr_t)out;
+  const bool overlap = in < to + n && to < in + n;
+  if (S < 2 || rows > 65535 || overlap) {
     hipLaunchKernelGGL(softmax_rows_kernel, dim3(rows), dim3(256), 0, st, logits, V, invT, out);
     return hipGetLastError();
   }

@@ -372,7 +372,7 @@ def accept_from_logits_noalloc(logits: torch.Tensor, drafts: torch.Tensor, draft
 
 def softmax_into(logits: torch.Tensor, out: torch.Tensor, temperature: float = 1.0) -> None:
     """out = softmax(logits / temperature) row by row (float32, last dim V),
-    on the current stream."""
+    on the current stream; out may be logits itself."""
     V = logits.shape[-1]
     rows = logits.numel() // V
     _check(load_library().spade_softmax(_ptr(logits), rows, V, float(temperature), _ptr(out), _stream()))

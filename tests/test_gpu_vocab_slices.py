@@ -91,3 +91,16 @@ def test_softmax_over_slices(model, V, offset):
     ref = torch.softmax(z[:3].double() / 0.8, -1)
     assert torch.allclose(out[:3].double(), ref, rtol=5e-6, atol=0)
     assert bool(out[3].isnan().all()) and bool(out[4].isnan().all())
+
+
+@pytest.mark.parametrize("V", [4096, 4097, 33001])
+def test_softmax_in_place(model, V):
+    """d_probs == d_logits gives what two buffers give (float64, the bound of
+    test_softmax_over_slices), whatever the vocabulary."""
+    import torch
+    from paper_2608_13076_amd import spade
+    g = torch.Generator(model.device).manual_seed(V)
+    z = 3.0 * torch.randn((3, V), device=model.device, generator=g)
+    ref = torch.softmax(z.double() / 0.8, -1)
+    spade.softmax_into(z, z, 0.8)
+    assert torch.allclose(z.double(), ref, rtol=5e-6, atol=0)
