@@ -281,7 +281,7 @@ spade_status spade_accept_from_logits(spade_model m, int B, int gamma, int V, co
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc --
  * and have no model: the same accept/reject and correction draw (the sliced
  * draw of a call that may sample) with the library's own static device
- * scratch (about 260 KB per device, held until the process ends) instead of
+ * scratch (about 790 KB per device, held until the process ends) instead of
  * a model's workspace.  B <= 64 (else SPADE_ECAPACITY), gamma + 1 <= 16;
  * other arguments as in spade_accept_from_logits.  d_err: device uint32 the
  * call ORs the SPADE_DERR_* bits into (the caller clears it).  Calls no

@@ -58,8 +58,8 @@ spade_status spade_model_set_attn_merge(spade_model m, int mode);
  * second launch over slices of 1024 tokens (at most 256 slices), one
  * workgroup per (slice, request), the last slice of a request to finish
  * taking the best of the slices; mode 1 keeps it in the request's accept
- * workgroup.  The single-launch pass always keeps it there.  Results are bit-for-bit the same under
- * every mode.  Other values return SPADE_EINVAL. */
+ * workgroup.  Results are bit-for-bit the same under every mode (the rows'
+ * statistics come from the same launch, whose cut depends on V alone).  Other values return SPADE_EINVAL. */
 spade_status spade_model_set_correction_slices(spade_model m, int mode);
 
 /* Grouped-query attention chunks.  For a model with G = heads / K/V heads

@@ -165,7 +165,7 @@ WsPlan plan_ws(const Dims& D, int max_batch, int max_gamma, int max_len) {
     p.tile_floats = (size_t)((std::max(D.d + 2 * D.dkv, 2 * D.F) / 16 + 15) / 16) * tile_split_floats();
   p.tile_part = take(p.tile_floats * 4);
   p.corr_lse = take((size_t)max_batch * 4);
-  p.corr_part = take((size_t)max_batch * kCorrMaxSlices * 4 * 4);
+  p.corr_part = take((size_t)max_batch * kCorrPartFloats * 4);
   p.corr_cnt = take((size_t)max_batch * 4);
   p.prefill_tok = take((size_t)p.Mrows * 4);
   p.prefill_cnt = take((size_t)max_batch * 4);

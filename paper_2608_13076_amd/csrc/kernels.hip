@@ -796,10 +796,10 @@ attn_prefill_kernel(AttnParams p, int ngrp) {
 // request.
 // ---------------------------------------------------------------------------
 // Statistics of given logits (spade_accept_from_logits) over slices of the
-// vocabulary: workgroup (slice, row) writes entry `slice` of the row.
+// vocabulary: workgroup row * NU + slice writes entry `slice` of the row.
 __global__ void __launch_bounds__(256) row_stats_kernel(AcceptParams p, int per, float* stats) {
   __shared__ RowStat part[4];
-  const int row = (int)blockIdx.y, s = (int)blockIdx.x;
+  const int row = (int)blockIdx.x / p.NU, s = (int)blockIdx.x - row * p.NU;
   const float invT = accept_samples(p, row / p.R) ? p.inv_T : 1.0f;
   const int v0 = s * per, v1 = min(p.V, v0 + per);
   const RowStat w = scan_stats<256, false>(p.logits + (size_t)row * p.V, v0, v1, invT);
@@ -808,7 +808,7 @@ __global__ void __launch_bounds__(256) row_stats_kernel(AcceptParams p, int per,
   if (threadIdx.x == 0) {
     RowStat st = part[0];
     for (int i = 1; i < 4; ++i) st = merge_stat(st, part[i]);
-    float* o = stats + ((size_t)row * gridDim.x + s) * 3;
+    float* o = stats + (size_t)blockIdx.x * 3;
     o[0] = st.m;
     o[1] = st.s;
     o[2] = __int_as_float(st.a);
@@ -1716,20 +1716,21 @@ hipError_t launch_forward(spade_model md, spade_kv kv, const ForwardCall& fc, hi
 
 namespace {
 
-// Calls with given logits that may sample (their scratch is this call's
-// anyway): the rows' statistics over slices of the vocabulary first, in the
-// memory of the correction's per-slice winners (at most 1024 floats a request;
-// the correction launch comes after they are read).  Greedy-only calls use no
+// Calls with given logits that may sample: the rows' statistics over slices of
+// the vocabulary first, in part, the memory of the correction's per-slice
+// winners (the correction launch comes after they are read).  The cut follows
+// from V alone, so a row's log-sum-exp does not depend on gamma, on the other
+// requests or on where the correction is drawn.  Greedy-only calls use no
 // scratch and scan their rows in the accept workgroup.
 constexpr int kStatSliceTokens = 4096;
 
-void launch_row_stats(AcceptParams& p, hipStream_t st) {
-  const int S = std::min((p.V + kStatSliceTokens - 1) / kStatSliceTokens, kCorrMaxSlices * 4 / (3 * p.R));
-  if (S < 2 || (long)p.B * p.R > 65535) return;
+void launch_row_stats(AcceptParams& p, float* part, hipStream_t st) {
+  const int S = std::min((p.V + kStatSliceTokens - 1) / kStatSliceTokens, kStatMaxSlices);
+  if (S < 2) return;
   const int per = ((p.V + S - 1) / S + 3) / 4 * 4;
-  hipLaunchKernelGGL(row_stats_kernel, dim3(S, p.B * p.R), dim3(256), 0, st, p, per, p.corr_part);
-  p.stats = p.corr_part;
   p.NU = S;
+  hipLaunchKernelGGL(row_stats_kernel, dim3((unsigned)S * p.B * p.R), dim3(256), 0, st, p, per, part);
+  p.stats = part;
   p.stat_stride = 3 * S;
   p.given = 1;
 }
@@ -1764,12 +1765,12 @@ hipError_t launch_accept(spade_model md, const AcceptCall& ac, hipStream_t st) {
   // the vocabulary, unless turned off (the accept workgroup then draws it)
   const bool may_sample = ac.u != nullptr && (ac.q != nullptr || ac.gamma == 0);
   const bool split = may_sample && md->corr_split != 1 && ac.B <= md->max_batch;
+  if (may_sample && ac.B <= md->max_batch && p.stats == nullptr) launch_row_stats(p, md->ws.corr_part, st);
   if (split) {
     p.corr_slices = std::min(kCorrMaxSlices, (ac.V + kCorrSliceTokens - 1) / kCorrSliceTokens);
     p.corr_lse = md->ws.corr_lse;
     p.corr_part = md->ws.corr_part;
     p.corr_cnt = md->ws.corr_cnt;
-    if (p.stats == nullptr) launch_row_stats(p, st);
   }
   hipLaunchKernelGGL(accept_kernel, dim3(ac.B), dim3(kAcceptThreads), 0, st, p);
   if (split) {
@@ -1792,7 +1793,7 @@ hipError_t launch_accept(spade_model md, const AcceptCall& ac, hipStream_t st) {
 struct NoAllocScratch {
   uint32_t cnt[kNoAllocMaxB];
   float lse[kNoAllocMaxB];
-  float part[kNoAllocMaxB * kCorrMaxSlices * 4];
+  float part[kNoAllocMaxB * kCorrPartFloats];
 };
 static __device__ __align__(256) uint8_t scratch[sizeof(NoAllocScratch)];
 
@@ -1852,7 +1853,7 @@ hipError_t launch_accept_noalloc(const AcceptCall& ac, uint32_t* err, hipStream_
     p.corr_cnt = (uint32_t*)(base + offsetof(NoAllocScratch, cnt));
     p.corr_lse = (float*)(base + offsetof(NoAllocScratch, lse));
     p.corr_part = (float*)(base + offsetof(NoAllocScratch, part));
-    launch_row_stats(p, st);
+    launch_row_stats(p, p.corr_part, st);
   }
   hipLaunchKernelGGL(accept_kernel, dim3(ac.B), dim3(kAcceptThreads), 0, st, p);
   if (may_sample) {

@@ -20,6 +20,10 @@ constexpr int kPrefillPack = 64;      // requests of a packed prefill forward
 constexpr int kPrefillAttnTiles = 4;   // 16-row tiles (one wave each) per workgroup of the prefill attention
 constexpr int kMaxR = 16;            // rows per request in one forward (gamma <= 15)
 constexpr int kCorrMaxSlices = 256; // vocabulary slices of one correction draw
+constexpr int kStatMaxSlices = 64;  // vocabulary slices of the statistics of given logits
+// scratch floats per request: the correction's winners or, before them, the slices' statistics
+constexpr int kCorrPartFloats = kMaxR * kStatMaxSlices * 3;
+static_assert(kCorrPartFloats >= kCorrMaxSlices * 4, "winners of the correction slices");
 constexpr int kNoAllocMaxB = 64;     // requests of one spade_accept_from_logits_noalloc call
 constexpr int kActSplits = 2;        // bf16 terms per fp32 activation (hi, lo)
 constexpr int kAttnChunk = 128;      // keys per workgroup of the generic attention (f32 cache or head_dim != 128)
@@ -135,7 +139,7 @@ struct Workspace {
   float* tile_part;     // [tile_floats] sums published by the k-split launches of the tiled GEMM
   size_t tile_floats;
   float* corr_lse;      // [Bmax] log-sum-exp of each sampling request's correction row
-  float* corr_part;     // [Bmax][kCorrMaxSlices][4] per-slice winners of the correction draw
+  float* corr_part;     // [Bmax][kCorrPartFloats] per-slice winners of the correction draw; slice statistics
   uint32_t* corr_cnt;   // [Bmax] arrival counters of the correction slices (kept at zero between calls)
   int32_t* prefill_tok; // [Mrows] token ids of one batched-prefill forward
   int32_t* prefill_cnt; // [Bmax] prompt tokens to cache per request (batched prefill)
