@@ -88,13 +88,12 @@ __device__ __forceinline__ bool accept_samples(const AcceptParams& p, int b) {
 }
 
 // (max, sum exp, argmax) of z = logit / T over tokens [v0, v1) of a row, by
-// all NT threads of the workgroup, 16 tokens per thread and step (16-byte
-// loads where the row allows them): the step's maximum first, then one
-// exponential per token.  NaN is skipped; ties keep the lower id.  Every
-// thread of a wave gets its wave's result.
+// NT threads (tid: the thread's number among them), 16 tokens per thread and
+// step (16-byte loads where the row allows them): the step's maximum first,
+// then one exponential per token.  NaN is skipped; ties keep the lower id.
+// The thread's own part; wave_stat combines a wave's.
 template <int NT, bool COH>
-__device__ __forceinline__ RowStat scan_stats(const float* row, int v0, int v1, float invT) {
-  const int tid = threadIdx.x;
+__device__ __forceinline__ RowStat scan_lane(const float* row, int v0, int v1, float invT, int tid) {
   const bool vec = !COH && ((size_t)(row + v0) & 15u) == 0u;
   RowStat st{-INFINITY, 0.f, 0x7fffffff};
   for (int base = v0; base < v1; base += NT * 16) {
@@ -132,6 +131,10 @@ __device__ __forceinline__ RowStat scan_stats(const float* row, int v0, int v1, 
     for (int k = 0; k < 16; ++k) e += z[k] == m ? 1.f : (z[k] < m ? expf(z[k] - m) : 0.f);
     if (a != 0x7fffffff) st = merge_stat(st, RowStat{m, m == -INFINITY ? 1.f : e, a});
   }
+  return st;
+}
+
+__device__ __forceinline__ RowStat wave_stat(RowStat st) {
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) {
     RowStat o;
@@ -141,6 +144,22 @@ __device__ __forceinline__ RowStat scan_stats(const float* row, int v0, int v1, 
     st = (threadIdx.x & off) ? merge_stat(o, st) : merge_stat(st, o);
   }
   return st;
+}
+
+// Rows of at most this many tokens: a wave scans a row in steps of 1024, or,
+// where the steps of all rows fit the workgroup's waves, a wave takes one step
+// and the steps' lanes are merged in the same order, so a sampling call's
+// log-sum-exp does not depend on gamma.
+constexpr int kScanShort = 4096;
+
+// A longer row is scanned in the accept workgroup only by greedy calls, whose
+// results no order changes: pieces of at most 8192 tokens, at least one for
+// every wave.  The rows one after the other, each by the whole workgroup (a
+// round trip and a reduction per row), took 75 us for 16 requests of 16 rows
+// of 1000 tokens and 79 for 5000 (greedy; now 11 and 23).
+__device__ __forceinline__ int scan_pieces(int V, int R) {
+  const int s = (V + 8191) / 8192, w = 16 / R;
+  return min(16, s > w ? s : w);
 }
 
 // The skinny LM head's row statistics from the per-panel statistics of the
@@ -175,14 +194,7 @@ __device__ __forceinline__ void fold_panels(float* row, int panels, int NU, RowS
   RowStat st{-INFINITY, 0.f, 0x7fffffff};
   for (int q = lane; q < NU; q += 64)
     if (ent[q].m != -INFINITY) st = merge_stat(st, ent[q]);
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    RowStat o;
-    o.m = __shfl_xor(st.m, off);
-    o.s = __shfl_xor(st.s, off);
-    o.a = __shfl_xor(st.a, off);
-    st = (lane & off) ? merge_stat(o, st) : merge_stat(st, o);
-  }
+  st = wave_stat(st);
   if (lane == 0) {
     row[0] = st.m;
     row[1] = st.s;
@@ -191,7 +203,7 @@ __device__ __forceinline__ void fold_panels(float* row, int panels, int NU, RowS
 }
 
 struct AcceptSmem {
-  RowStat scan[kMaxR][16];  // given logits only: per row and wave
+  RowStat scan[16][64];  // given logits only: per wave and lane, or per row and piece
   float rlse[kMaxR];
   int rarg[kMaxR];
   int x[kMaxR];                     // draft tokens (clamped)
@@ -226,13 +238,23 @@ __device__ __forceinline__ void accept_request(const AcceptParams& p, int b, Acc
     }
   }
 
-  if (p.stats == nullptr) {
-    // given logits: the whole workgroup scans each row (a greedy-only call
-    // uses no scratch; the others come with row_stats_kernel's slices).  16
-    // requests x 9 rows of 128256 logits took 816 us with a wave per row
-    for (int r = 0; r < R; ++r) {
-      const RowStat st = scan_stats<NT, COH>(lg + (size_t)r * V, 0, V, invT);
-      if (lane == 0) sm.scan[r][wave] = st;
+  // given logits of a short vocabulary or of a greedy-only call (which uses no
+  // scratch; the others come with row_stats_kernel's slices)
+  const int steps = (V + 1023) / 1024;
+  const bool lanes = V <= kScanShort && R * steps <= NWV;
+  const int pieces = V <= kScanShort ? 1 : scan_pieces(V, R);
+  if (p.stats == nullptr && lanes) {
+    if (wave < R * steps) {
+      const int r = wave / steps, v0 = (wave - r * steps) * 1024;
+      sm.scan[wave][lane] = scan_lane<64, COH>(lg + (size_t)r * V, v0, min(V, v0 + 1024), invT, lane);
+    }
+    __syncthreads();
+  } else if (p.stats == nullptr) {
+    const int per = ((V + pieces - 1) / pieces + 3) / 4 * 4;
+    for (int i = wave; i < R * pieces; i += NWV) {
+      const int r = i / pieces, v0 = (i - r * pieces) * per;
+      const RowStat st = wave_stat(scan_lane<64, COH>(lg + (size_t)r * V, v0, min(V, v0 + per), invT, lane));
+      if (lane == 0) sm.scan[r][i - r * pieces] = st;
     }
     __syncthreads();
   }
@@ -251,17 +273,12 @@ __device__ __forceinline__ void accept_request(const AcceptParams& p, int b, Acc
         // (given logits may be -inf throughout: the lowest id then)
         if (one.m != -INFINITY || p.given) st = merge_stat(st, one);
       }
-    } else if (lane < NWV) {
+    } else if (lanes) {
+      for (int s = 0; s < steps; ++s) st = merge_stat(st, sm.scan[r * steps + s][lane]);
+    } else if (lane < pieces) {
       st = sm.scan[r][lane];
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-      RowStat o;
-      o.m = __shfl_xor(st.m, off);
-      o.s = __shfl_xor(st.s, off);
-      o.a = __shfl_xor(st.a, off);
-      st = (lane & off) ? merge_stat(o, st) : merge_stat(st, o);
-    }
+    if (p.stats != nullptr || lanes || pieces > 1) st = wave_stat(st);
     if (lane == 0) {
       sm.rlse[r] = st.m + logf(st.s);
       sm.rarg[r] = st.a;

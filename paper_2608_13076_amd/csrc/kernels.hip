@@ -802,7 +802,7 @@ __global__ void __launch_bounds__(256) row_stats_kernel(AcceptParams p, int per,
   const int row = (int)blockIdx.x / p.NU, s = (int)blockIdx.x - row * p.NU;
   const float invT = accept_samples(p, row / p.R) ? p.inv_T : 1.0f;
   const int v0 = s * per, v1 = min(p.V, v0 + per);
-  const RowStat w = scan_stats<256, false>(p.logits + (size_t)row * p.V, v0, v1, invT);
+  const RowStat w = wave_stat(scan_lane<256, false>(p.logits + (size_t)row * p.V, v0, v1, invT, (int)threadIdx.x));
   if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = w;
   __syncthreads();
   if (threadIdx.x == 0) {

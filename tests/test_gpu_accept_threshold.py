@@ -40,7 +40,7 @@ def _accepted_p(call, logits, drafts, q, G):
     return hi.cpu().numpy()
 
 
-@pytest.mark.parametrize("V", [1001, 4096, 4097, 20000, 65999])
+@pytest.mark.parametrize("V", [1001, 1025, 3072, 4096, 4097, 20000, 65999])
 def test_accept_probability_bit_identical(model, V):
     import torch
     from paper_2608_13076_amd import spade

@@ -24,7 +24,8 @@ def model():
     return spade.Model(shape, max_batch=4, max_gamma=15, max_len=64)
 
 
-@pytest.mark.parametrize("V,G", [(4095, 2), (4097, 3), (8193, 0), (16385, 15), (39999, 5)])
+@pytest.mark.parametrize("V,G", [(33, 15), (1024, 15), (1025, 1), (3071, 4), (4095, 2), (4096, 15),
+                                  (4097, 3), (8193, 0), (16385, 15), (39999, 5)])
 @pytest.mark.parametrize("sampling", [False, True])
 def test_accept_over_slices(model, V, G, sampling):
     import torch
