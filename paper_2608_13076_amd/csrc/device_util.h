@@ -71,6 +71,12 @@ __device__ __forceinline__ uint4 ld_stream_g128(const void* p) {
   return __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4*)p));
 }
 
+// Four consecutive floats at any float's address: one 16-byte access (global
+// memory takes them at 4-byte alignment).
+struct alignas(4) Float4u {
+  float v[4];
+};
+
 template <bool COH>
 __device__ __forceinline__ float ld_f32(Rsrc r, uint32_t off) {
   return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, COH ? kAuxCoh : 0));

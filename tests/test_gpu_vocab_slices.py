@@ -105,3 +105,21 @@ def test_softmax_in_place(model, V):
     ref = torch.softmax(z.double() / 0.8, -1)
     spade.softmax_into(z, z, 0.8)
     assert torch.allclose(z.double(), ref, rtol=5e-6, atol=0)
+
+
+@pytest.mark.parametrize("rows,V", [(600, 5119), (600, 5121), (5, 7167), (5, 7169), (513, 12289)])
+@pytest.mark.parametrize("offset", [0, 3])
+def test_softmax_where_its_cut_changes(model, rows, V, offset):
+    """Against float64; nothing outside the output is written.  Scaled logits
+    lie within 20 of 0 and 40 of their maximum: 1 / 0.8 is off by 2^-25 of
+    itself (1.2e-6), the two products by 20 * 2^-24 each (2.4e-6), their
+    difference by 2^-19 (1.9e-6); the exponential and the sum add under 1e-6."""
+    import torch
+    from paper_2608_13076_amd import spade
+    g = torch.Generator(model.device).manual_seed(rows + V)
+    z = 3.0 * torch.randn(rows * V + 4, device=model.device, generator=g)[offset:offset + rows * V].view(rows, V)
+    buf = torch.full((rows * V + 8,), 7.0, device=model.device)
+    out = buf[offset:offset + rows * V].view(rows, V)
+    spade.softmax_into(z, out, 0.8)
+    assert torch.allclose(out.double(), torch.softmax(z.double() / 0.8, -1), rtol=7e-6, atol=0)
+    assert bool((buf[:offset] == 7.0).all()) and bool((buf[offset + rows * V:] == 7.0).all())
