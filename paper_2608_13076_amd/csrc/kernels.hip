@@ -1914,11 +1914,15 @@ hipError_t launch_pack(spade_model md, int kind, int layer, const void* src, hip
 }
 
 hipError_t launch_softmax(const float* logits, int rows, int V, float invT, float* out, hipStream_t st) {
-  // slices from two of them on (every slice then holds more than 1000
-  // tokens); shorter rows, more rows than a grid's y dimension and in-place
-  // calls (the slices' scratch lies in the output before the last read of the
-  // logits) in one workgroup each
-  const int S = std::min(kSoftmaxMaxSlices, (V + kSoftmaxSlice - 1) / kSoftmaxSlice);
+  // slices from where three launches cost less than one workgroup per row (us,
+  // one workgroup / slices: 1 row of 6144 tokens 11.9 / 11.7-13.4, of 8192 16.2
+  // / 11.8-13.3; 512 rows of 5000 13.2 / 13.8, of 5500 20.0 / 14.2; 4096 rows
+  // of 4500 49.1 / 51.5, of 5500 59.1 / 56.3): every slice then holds more
+  // than 1000 tokens.  Shorter rows, more rows than a grid's y dimension and
+  // in-place calls (the slices' scratch lies in the output before the last
+  // read of the logits) take one workgroup each
+  const int from = rows < 512 ? 7168 : 5120;
+  const int S = V < from ? 1 : std::min(kSoftmaxMaxSlices, (V + kSoftmaxSlice - 1) / kSoftmaxSlice);
   const uintptr_t n = (uintptr_t)rows * V * 4, in = (uintptr_t)logits, to = (uintptr_t)out;
   const bool overlap = in < to + n && to < in + n;
   if (S < 2 || rows > 65535 || overlap) {
