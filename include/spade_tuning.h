@@ -153,6 +153,12 @@ spade_status spade_profile_gemm(spade_model m, spade_kv kv, int kind, int B, int
 spade_status spade_wide_tiling(int kind, int rows, int n_units, int k, int n_cu, int* row_tiles, int* panels,
                                int* k_splits);
 
+/* The same for the tiled GEMM: 16-row tiles and panels per wave of a
+ * workgroup and k-splits of a launch, with every setting at its default and a
+ * workspace large enough for any k-split. */
+spade_status spade_tile_tiling(int kind, int rows, int n_units, int k, int n_cu, int* row_tiles, int* panels,
+                               int* k_splits);
+
 #ifdef __cplusplus
 }
 #endif

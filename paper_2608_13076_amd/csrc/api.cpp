@@ -693,6 +693,19 @@ spade_status spade_wide_tiling(int kind, int rows, int n_units, int k, int n_cu,
   return SPADE_OK;
 }
 
+spade_status spade_tile_tiling(int kind, int rows, int n_units, int k, int n_cu, int* row_tiles, int* panels,
+                               int* k_splits) {
+  if (!row_tiles || !panels || !k_splits) return fail(SPADE_EINVAL, "null pointer");
+  if (kind < GEMM_QKV || kind > GEMM_LM || rows <= kWideMinRows || n_units < 1 || k < 256 || k % 256 != 0 ||
+      n_cu < 1)
+    return fail(SPADE_EINVAL, "shape out of range");
+  const TileChoice c = tile_choice(kind, rows, n_units, k / 256, n_cu, 0, (size_t)-1);
+  *row_tiles = c.rt;
+  *panels = c.p;
+  *k_splits = c.ks;
+  return SPADE_OK;
+}
+
 spade_status spade_get_device_error(spade_model m, uint32_t* h_flags, void* stream) {
   if (!m || !h_flags) return fail(SPADE_EINVAL, "null pointer");
   hipStream_t st = (hipStream_t)stream;

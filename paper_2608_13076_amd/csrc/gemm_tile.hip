@@ -99,7 +99,8 @@ hipError_t launch_tile_kind(const GemmParams& gp, const TileChoice& c, float* pa
 // The tiles that are built, each with the time one workgroup takes for a 32-k
 // slice (us).  Fitted, with the constants of tile_choice, to 490 launches of
 // the 7B and 8B projections at 144, 1019 and 2040 rows over every tile and
-// k-split (rms error 9%; the picks within 5% of the fastest of each shape).
+// k-split (rms error 9%; the picks within 5% of the fastest of each of those
+// shapes; an LM head of 128K columns takes a fifth to a quarter more).
 struct TileCost {
   int rt, p;
   double slice_us;
@@ -111,16 +112,23 @@ constexpr TileCost kTileCosts[] = {{2, 2, 0.362}, {3, 2, 0.418}, {4, 2, 0.479}, 
 }  // namespace
 
 // Tile and k-splits of a launch: the least estimate of
-//   rounds of workgroups (one per compute unit at a time)
+//   rounds of workgroups (one per compute unit at a time, the panel groups of
+//   an XCD on its eighth of them)
 //     x (slices of the longest k-split x the tile's time per slice + 2 us)
 //   + 3 us, and for k-splits 5 us more for the second launch and the
 //   published values written and read back at 8 TB/s,
-// but no less than the weights at 5.5 TB/s.  cap_floats: the published
-// values that fit the workspace; fixed_ks > 0: that many splits (one where
+// but no less than the weights at 5.5 TB/s; ties, several tiles below that
+// line, go to the least time of the rounds.  Rounds over the whole chip let 20
+// panel groups pass for one where four XCDs had 36 workgroups for 32 compute
+// units (13B O and down at 144 rows 48 and 97 us, now 39 and 55; 880 rows 150
+// and 363, now 89 and 199); ties to the first tile listed took the 33B LM head
+// at 33 rows 97 us (now 77).  cap_floats: the published values that fit the workspace; fixed_ks > 0: that many splits (one where
 // they do not fit).
 TileChoice tile_choice(int kind, int M, int n_units, int NKB, int n_cu, int fixed_ks, size_t cap_floats) {
   const int tiles = (M + 15) / 16;
+  const int xcd_cu = std::max(1, n_cu / 8);
   TileChoice best{2, 2, 1, -1.0};
+  double best_cu = 0.0;
   for (const TileCost& t : kTileCosts) {
     const int nug = gemm_tile_unit_groups(n_units, t.p), nrg = gemm_tile_row_groups(M, t.rt);
     for (int ks = 1; ks <= 8; ++ks) {
@@ -132,11 +140,14 @@ TileChoice tile_choice(int kind, int M, int n_units, int NKB, int n_cu, int fixe
         longest = std::max(longest, NKB * (8 * (s + 1) / ks) / 8 - NKB * (8 * s / ks) / 8);
         if (s > 0) slots += 8 * (s + 1) / ks - 8 * s / ks;
       }
-      const long rounds = ((long)nug * nrg * ks + n_cu - 1) / n_cu;
-      double us = rounds * (longest * 8 * t.slice_us + 2.0);
-      us = std::max(us, (double)n_units * NKB * 8192.0 / 5.5e6) + 3.0;
+      const long rounds = ((long)((nug + 7) / 8) * nrg * ks + xcd_cu - 1) / xcd_cu;
+      const double cu = rounds * (longest * 8 * t.slice_us + 2.0);
+      double us = std::max(cu, (double)n_units * NKB * 8192.0 / 5.5e6) + 3.0;
       if (ks > 1) us += 5.0 + item * 4.0 / 8.0 * slots * 2.0 / 8e6;
-      if (best.us < 0 || us < best.us - 1e-9) best = TileChoice{t.rt, t.p, ks, us};
+      if (best.us < 0 || us < best.us - 1e-9 || (us <= best.us + 1e-9 && cu < best_cu - 1e-9)) {
+        best = TileChoice{t.rt, t.p, ks, us};
+        best_cu = cu;
+      }
     }
   }
   if (best.us < 0) return tile_choice(kind, M, n_units, NKB, n_cu, 1, cap_floats);

@@ -39,7 +39,7 @@ EXPORTED_TUNING = (
     "spade_model_set_wide_tiles", "spade_model_set_wide_k_splits", "spade_model_set_split_k",
     "spade_model_set_attn_merge", "spade_model_set_correction_slices", "spade_model_set_attn_grouped",
     "spade_model_set_prefill_rows", "spade_model_set_big_gemm", "spade_model_set_mid_gemm", "spade_profile_gemm",
-    "spade_wide_tiling",
+    "spade_wide_tiling", "spade_tile_tiling",
 )
 
 
@@ -109,6 +109,7 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
         "spade_softmax": (I, [P, I, I, F, P, P]),
         "spade_prefill_batch": (I, [P, P, I, P, I, P, P]),
         "spade_wide_tiling": (I, [I, I, I, I, I, P, P, P]),
+        "spade_tile_tiling": (I, [I, I, I, I, I, P, P, P]),
         "spade_last_error": (ctypes.c_char_p, []),
         "spade_model_destroy": (None, [P]),
         "spade_kv_destroy": (None, [P]),
@@ -396,6 +397,16 @@ def wide_tiling(kind: str, rows: int, n_units: int, k: int, n_cu: int = 256) -> 
     lib = load_library()
     rt, p, ks = ctypes.c_int(), ctypes.c_int(), ctypes.c_int()
     _check(lib.spade_wide_tiling(GEMM_KINDS[kind], rows, n_units, k, n_cu, ctypes.byref(rt), ctypes.byref(p),
+                                 ctypes.byref(ks)))
+    return rt.value, p.value, ks.value
+
+
+def tile_tiling(kind: str, rows: int, n_units: int, k: int, n_cu: int = 256) -> tuple:
+    """(row tiles, panels per wave, k-splits) the tiled GEMM picks for a
+    projection of `rows` rows, `n_units` weight panels and `k` inputs."""
+    lib = load_library()
+    rt, p, ks = ctypes.c_int(), ctypes.c_int(), ctypes.c_int()
+    _check(lib.spade_tile_tiling(GEMM_KINDS[kind], rows, n_units, k, n_cu, ctypes.byref(rt), ctypes.byref(p),
                                  ctypes.byref(ks)))
     return rt.value, p.value, ks.value
 

@@ -128,3 +128,20 @@ def test_wide_tiling_splits_narrow_projections(lib):
         spade.wide_tiling("o", 16, 256, 4096)
     with pytest.raises(spade.SpadeError):
         spade.wide_tiling("o", 64, 256, 4000)
+
+
+def test_tile_tiling_counts_the_rounds_of_an_xcd(lib):
+    """Panel groups go to eight XCDs of 32 compute units.  The 13B shape's 20
+    or 40 leave them uneven: the picks for its O and down projections keep the
+    fullest XCD to one round where some tile does.  Where several tiles are as
+    fast as the weights arrive (the 33B LM head of few rows), the one with the
+    least work per compute unit is picked, not the first."""
+    for rows in (96, 112, 128, 144):
+        for kind, k in (("o", 5120), ("down", 13824)):
+            rt, p, ks = spade.tile_tiling(kind, rows, 320, k)
+            groups = -(-320 // (8 * p))
+            assert -(-groups // 8) * -(-(-(-rows // 16)) // rt) * ks <= 32, (rows, kind, rt, p, ks)
+    assert spade.tile_tiling("lm", 33, 2000, 6656) == (4, 1, 1)
+    for bad in (("o", 16, 256, 4096), ("o", 64, 256, 4000), ("o", 64, 0, 4096)):
+        with pytest.raises(spade.SpadeError):
+            spade.tile_tiling(*bad)
