@@ -32,8 +32,9 @@ extern "C" {
  * shape and the compute-unit count; row_tiles 1..3 and panels 1..2 fix them
  * (the O and down projections, which can be k-split, take two panels per
  * wave with at most two row tiles and fall back to one tile and one panel);
- * row_tiles = -1 turns the wide-row GEMM off (the skinny engine then runs
- * once per 32 rows and streams the weights once per launch).  Results are
+ * row_tiles = -1 turns the wide-row GEMM off, and the tiled one up to 144 rows
+ * unless it is forced there: the skinny engine then runs once per 32 rows and
+ * streams the weights once per launch.  Results are
  * bit-for-bit the same under every setting: a row's dot products are summed
  * over the same k-ranges in the same order whatever the tiling.  Other values
  * return SPADE_EINVAL. */
@@ -158,6 +159,11 @@ spade_status spade_wide_tiling(int kind, int rows, int n_units, int k, int n_cu,
  * workspace large enough for any k-split. */
 spade_status spade_tile_tiling(int kind, int rows, int n_units, int k, int n_cu, int* row_tiles, int* panels,
                                int* k_splits);
+
+/* Inspection hook (host only): the engine that a projection launch of `rows`
+ * rows takes under the model's present settings: 0 the skinny one (16 or 32
+ * rows per launch, or k-split), 1 the wide-row GEMM, 2 the tiled GEMM. */
+spade_status spade_model_gemm_engine(spade_model m, int kind, int rows, int* engine);
 
 #ifdef __cplusplus
 }

@@ -693,6 +693,13 @@ spade_status spade_wide_tiling(int kind, int rows, int n_units, int k, int n_cu,
   return SPADE_OK;
 }
 
+spade_status spade_model_gemm_engine(spade_model m, int kind, int rows, int* engine) {
+  if (!m || !engine) return fail(SPADE_EINVAL, "null pointer");
+  if (kind < GEMM_QKV || kind > GEMM_LM || rows < 1) return fail(SPADE_EINVAL, "shape out of range");
+  *engine = gemm_engine(m, kind, rows);
+  return SPADE_OK;
+}
+
 spade_status spade_tile_tiling(int kind, int rows, int n_units, int k, int n_cu, int* row_tiles, int* panels,
                                int* k_splits) {
   if (!row_tiles || !panels || !k_splits) return fail(SPADE_EINVAL, "null pointer");

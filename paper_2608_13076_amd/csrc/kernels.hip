@@ -1180,7 +1180,7 @@ int split_k_choice(const GemmParams& gp, int n_cu, int fixed) {
 int lm_stats_panels(spade_model md, int M) {
   const Dims& D = md->dims;
   if (D.wdt != SPADE_BF16) return 0;
-  if (M > kWideMinRows) return md->wide_rt >= 0 ? D.Vpad / 16 : 0;
+  if (M > kWideMinRows) return gemm_engine(md, GEMM_LM, M) != ENGINE_SKINNY ? D.Vpad / 16 : 0;
   if (md->split_ks < 0) return 0;
   GemmParams gp{};
   gp.M = M;
@@ -1371,17 +1371,28 @@ constexpr int kTileMidRows = 144;
 bool tile_wins(int M) { return M > 32; }
 
 // Whether a launch of M rows runs on the tiled GEMM: where it measured faster
-// than the wide-row one, unless a setting turns it off or fixes the other
-// engine's schedule; the LM head only where the accept step expects per-panel
-// statistics.
+// than the wide-row one, unless a setting turns it off, fixes the other
+// engine's schedule or (batched verification) asks for the skinny engine; the
+// LM head only where the accept step expects per-panel statistics.
 bool runs_tiled(spade_model md, int kind, int M) {
   if (md->dims.wdt != SPADE_BF16 || M <= kWideMinRows) return false;
-  const bool lm = kind == GEMM_LM;
+  const bool lm = kind == GEMM_LM, skinny = md->wide_rt < 0;
   int mode = M <= kTileMidRows ? md->mid_gemm : md->big_gemm;
   if (md->big_gemm == 2 || mode == 2) mode = lm ? 0 : 2;
-  const bool wide_fixed = md->wide_rt > 0 || md->wide_p > 0 || md->wide_ks > 0;
-  return mode != 1 && !(lm && md->wide_rt < 0) && (mode == 2 || (!wide_fixed && (md->wide_rt < 0 || tile_wins(M))));
+  if (mode == 1 || (lm && skinny)) return false;
+  if (mode == 2) return true;
+  if (skinny) return M > kTileMidRows;
+  return md->wide_rt == 0 && md->wide_p == 0 && md->wide_ks == 0 && tile_wins(M);
 }
+
+}  // namespace
+
+int gemm_engine(spade_model md, int kind, int M) {
+  if (runs_tiled(md, kind, M)) return ENGINE_TILED;
+  return md->dims.wdt == SPADE_BF16 && M > kWideMinRows && md->wide_rt >= 0 ? ENGINE_WIDE : ENGINE_SKINNY;
+}
+
+namespace {
 
 template <bool ABF16, int NS>
 hipError_t launch_attn_prefill_ns(const AttnParams& ap, hipStream_t st) {
@@ -1513,8 +1524,9 @@ hipError_t launch_layer_gemm(spade_model md, spade_kv kv, int kind, int layer, c
   }
   const int grid = std::min(units, md->gemm_wgs);
   g.NU = grid;  // LM head: one statistics entry per workgroup and row
-  if (kind == GEMM_QKV && fc.row_map != nullptr && !runs_tiled(md, kind, M)) return hipErrorInvalidValue;
-  if (runs_tiled(md, kind, M)) {
+  const int engine = gemm_engine(md, kind, M);
+  if (kind == GEMM_QKV && fc.row_map != nullptr && engine != ENGINE_TILED) return hipErrorInvalidValue;
+  if (engine == ENGINE_TILED) {
     // the last layer of a prefill needs no query panels
     if (kind == GEMM_QKV && fc.tokens != nullptr && !fc.want_logits && layer + 1 == D.L) {
       g.unit0 = D.d / 16;
@@ -1534,7 +1546,7 @@ hipError_t launch_layer_gemm(spade_model md, spade_kv kv, int kind, int layer, c
     gp.act_stride = K;
     return launch_tile(kind, gp, c, W.tile_part, st);
   }
-  if (wb && M > kWideMinRows && md->wide_rt >= 0) {
+  if (engine == ENGINE_WIDE) {
     // batched rows: every row in one launch, weights streamed once
     GemmParams gp = g;
     gp.w = wmat;
@@ -2006,7 +2018,7 @@ hipError_t launch_prefill_batch(spade_model md, spade_kv kv, int B, const int32_
       R = std::max(R, pc.n[nb]);
     }
     const bool packed = md->dims.kvdt == SPADE_BF16 && md->dims.hd == kAttnHd && R > kAttnRows &&
-                        runs_tiled(md, GEMM_QKV, rows);
+                        gemm_engine(md, GEMM_QKV, rows) == ENGINE_TILED;
     if (!packed) {
       R = std::min(rem[b0], r_cap);
       nb = 1;

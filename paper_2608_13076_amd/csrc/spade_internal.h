@@ -244,6 +244,9 @@ size_t tile_split_floats();
 struct GemmParams;
 hipError_t launch_tile(int kind, const GemmParams& gp, const TileChoice& c, float* part, hipStream_t st);
 int lm_stats_panels(spade_model m, int M);
+// engine of a projection launch of M rows (small batches split along K count as skinny)
+enum { ENGINE_SKINNY = 0, ENGINE_WIDE = 1, ENGINE_TILED = 2 };
+int gemm_engine(spade_model m, int kind, int M);
 hipError_t launch_softmax(const float* logits, int rows, int V, float invT, float* out, hipStream_t st);
 hipError_t launch_prefill_batch(spade_model md, spade_kv kv, int B, const int32_t* tokens, int ld,
                                 const int* n_cache, hipStream_t st);

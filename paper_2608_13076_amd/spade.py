@@ -39,7 +39,7 @@ EXPORTED_TUNING = (
     "spade_model_set_wide_tiles", "spade_model_set_wide_k_splits", "spade_model_set_split_k",
     "spade_model_set_attn_merge", "spade_model_set_correction_slices", "spade_model_set_attn_grouped",
     "spade_model_set_prefill_rows", "spade_model_set_big_gemm", "spade_model_set_mid_gemm", "spade_profile_gemm",
-    "spade_wide_tiling", "spade_tile_tiling",
+    "spade_wide_tiling", "spade_tile_tiling", "spade_model_gemm_engine",
 )
 
 
@@ -110,6 +110,7 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
         "spade_prefill_batch": (I, [P, P, I, P, I, P, P]),
         "spade_wide_tiling": (I, [I, I, I, I, I, P, P, P]),
         "spade_tile_tiling": (I, [I, I, I, I, I, P, P, P]),
+        "spade_model_gemm_engine": (I, [P, I, I, P]),
         "spade_last_error": (ctypes.c_char_p, []),
         "spade_model_destroy": (None, [P]),
         "spade_kv_destroy": (None, [P]),
@@ -190,7 +191,8 @@ class Model:
 
     def set_wide_tiles(self, row_tiles: int, panels: int = 0) -> None:
         """Tiling of the batched projections: 16-row tiles per workgroup (0
-        chosen per launch, 1..3 fixed, -1 skinny engine once per 32 rows) and
+        chosen per launch, 1..3 fixed, -1 skinny engine once per 32 rows up to
+        144 rows) and
         weight panels per wave (0 chosen per launch, 1..2 fixed)."""
         _check(self.lib.spade_model_set_wide_tiles(self.handle, int(row_tiles), int(panels)))
 
@@ -234,6 +236,13 @@ class Model:
         """K splits of the small-batch projections whose operand does not fit
         in LDS: 0 chosen per launch, 2 or 4 fixed, -1 off."""
         _check(self.lib.spade_model_set_split_k(self.handle, int(splits)))
+
+    def gemm_engine(self, kind: str, rows: int) -> int:
+        """Engine of a projection launch of `rows` rows under the present
+        settings: 0 skinny, 1 wide-row, 2 tiled."""
+        e = ctypes.c_int()
+        _check(self.lib.spade_model_gemm_engine(self.handle, GEMM_KINDS[kind], int(rows), ctypes.byref(e)))
+        return e.value
 
     def device_error(self) -> int:
         v = ctypes.c_uint32()

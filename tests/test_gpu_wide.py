@@ -3,11 +3,12 @@
 Every tiling of the wide-row engine (1, 2 or 3 sixteen-row tiles per
 workgroup with 1 weight panel per wave, 1 or 2 with 2 panels, and the
 per-launch choice), each with the O and down projections unsplit or cut
-into 2 or 4 k-splits, must give bit-for-bit the logits, n_accepted and
-corrections of the skinny engine run once per 32 rows: all sum each dot
-product over the same eight k-ranges in the same order.  The mini shape's O
+into 2 or 4 k-splits, and the default (the tiled engine at these rows), must
+give bit-for-bit the logits, n_accepted and corrections of the skinny engine
+run once per 32 rows: all sum each dot product over the same eight k-ranges in
+the same order.  The mini shape's O
 projection has 4 k-blocks (empty k-ranges, splits without k-blocks) and its
-down projection 11.  The per-launch choice is also compared with the oracle
+down projection 11.  The default is also compared with the oracle
 to the usual bar, at 35 rows (B=5, gamma 6) and at 144 rows (B=16, gamma 8,
 the batched-serving shape).
 """
@@ -35,6 +36,7 @@ def _wide_workloads():
 
 @pytest.mark.parametrize("w", _wide_workloads(), ids=lambda w: w.name)
 def test_wide_tilings_bit_identical_and_match_oracle(w):
+    from paper_2608_13076_amd import spade
     weights = ModelWeights(w.model, w.seed)
     inp = make_inputs(w)
     orun = oracle_run(w, inp, weights=weights)  # also completes the chain drafts
@@ -47,13 +49,20 @@ def test_wide_tilings_bit_identical_and_match_oracle(w):
                   flush=True)
             model.set_wide_tiles(*tiles)
             model.set_wide_k_splits(ks)
+            model.set_mid_gemm(1 if tiles == (0, 0) else 0)
+            want = 0 if tiles[0] < 0 else 1
+            assert all(model.gemm_engine(k, w.batch * (w.gamma + 1)) == want for k in spade.GEMM_KINDS), (tiles, ks)
             runs[tiles + (ks,)] = gpu_verify(model, kv, inp)[:3]
+    model.set_mid_gemm(0)
+    model.set_wide_k_splits(0)
+    assert all(model.gemm_engine(k, w.batch * (w.gamma + 1)) == 2 for k in spade.GEMM_KINDS)
+    runs["default"] = gpu_verify(model, kv, inp)[:3]
     ref = runs[(-1, 0, 0)]
     for cfg, (lg, n, c) in runs.items():
         assert np.array_equal(lg.view(np.uint32), ref[0].view(np.uint32)), cfg
         assert np.array_equal(n, ref[1]) and np.array_equal(c, ref[2]), cfg
-    p = compare(orun, *runs[(0, 0, 0)])
-    print(f"[{w.name}] logit err {p.logit_err:.2e}, n {runs[(0, 0, 0)][1].tolist()}", flush=True)
+    p = compare(orun, *runs["default"])
+    print(f"[{w.name}] logit err {p.logit_err:.2e}, n {runs['default'][1].tolist()}", flush=True)
     assert p.logit_err < LOGIT_TOL[w.model.weight_dtype]
     assert not p.stable_n_fail and not p.stable_corr_fail, p
     assert model.device_error() == 0
