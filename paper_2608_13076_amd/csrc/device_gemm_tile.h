@@ -467,7 +467,7 @@ struct GemmTile {
     rnext = r_lo + 1;
     bnd = NKB * rnext / kGemmWaves;
     while (bnd == kb0 && rnext < r_hi) bnd = (NKB * ++rnext) / kGemmWaves;
-    // wave w moves blocks w, w + 4, ... of a slot's 4 RT: 8 rows x 128 bytes
+    // wave w moves blocks w, w + 8, ... of a slot's 4 RT: 8 rows x 128 bytes
     // (whole lines of the row-major operand), one 16-byte piece per lane
     // (lane l: row l / 8, piece l % 8 of the swizzled block).  Rows past M
     // repeat row M - 1: finite values whose products are never stored.
@@ -525,10 +525,11 @@ struct GemmTile {
   // No fragment read may be in flight where the control flow branches or
   // joins: the compiler takes an asm output as written at once and may copy
   // it to another register there.
+  template <int N = NX>
   __device__ __forceinline__ void lds_drain() {
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int i = 0; i < NX; ++i) lds_wait<0>(x[i]);
+    for (int i = 0; i < N; ++i) lds_wait<0>(x[i]);
     __builtin_amdgcn_sched_barrier(0);
   }
 
@@ -718,6 +719,7 @@ struct GemmTile {
       read_tile<0>(b0, x[0]);
       read_tile<1>(b0, x[1]);
       if constexpr (PF > 2) read_tile<2 % RT>(b0, x[2]);
+      lds_drain<PF>();
       for (int kb = kb0; kb < kb1; ++kb) kblock(kb, std::make_integer_sequence<int, 7>{});
     }
     if constexpr (SPLIT) {
