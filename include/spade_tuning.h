@@ -108,6 +108,14 @@ spade_status spade_model_set_big_gemm(spade_model m, int mode);
  * SPADE_EINVAL. */
 spade_status spade_model_set_mid_gemm(spade_model m, int mode, int k_splits);
 
+/* The tile of the tiled GEMM wherever it runs: row_tiles 16-row tiles a
+ * workgroup and panels 16-column panels a wave -- (2, 3, 4, 5, 6, 8 or 9, 2) or
+ * (4, 5, 6, 7 or 9, 1) -- and k_splits 1..8 (none for the LM head, and one
+ * where the workspace does not hold more); 0 and 0, and k_splits 0, are chosen
+ * per launch (the defaults).  Results are bit-for-bit the same under every
+ * setting.  Other values return SPADE_EINVAL. */
+spade_status spade_model_set_tile_gemm(spade_model m, int row_tiles, int panels, int k_splits);
+
 /* K splitting of the batched O and down projections on the wide-row GEMM.
  * Their weights have few panels (d_model / 16), so one workgroup per panel
  * group leaves most compute units idle; with `splits` = 2 or 4 each

@@ -238,6 +238,9 @@ spade_status spade_model_create(const spade_config* cfg, void* d_weights, void* 
   m->big_gemm = 0;
   m->mid_gemm = 0;
   m->mid_ks = 0;
+  m->tile_rt = 0;
+  m->tile_p = 0;
+  m->tile_ks = 0;
   if (const char* ev = std::getenv("SPADE_GEMM_WGS")) {
     const int v = std::atoi(ev);
     if (v > 0) m->gemm_wgs = std::min(v, kMaxStatGroups);
@@ -530,6 +533,17 @@ spade_status spade_model_set_mid_gemm(spade_model m, int mode, int k_splits) {
   return SPADE_OK;
 }
 
+spade_status spade_model_set_tile_gemm(spade_model m, int row_tiles, int panels, int k_splits) {
+  if (!m) return fail(SPADE_EINVAL, "null model");
+  if ((row_tiles != 0 || panels != 0) && !tile_built(row_tiles, panels))
+    return fail(SPADE_EINVAL, "no tile of %d row tiles and %d panels", row_tiles, panels);
+  if (k_splits < 0 || k_splits > 8) return fail(SPADE_EINVAL, "k_splits must be 0..8");
+  m->tile_rt = row_tiles;
+  m->tile_p = panels;
+  m->tile_ks = k_splits;
+  return SPADE_OK;
+}
+
 spade_status spade_model_set_correction_slices(spade_model m, int mode) {
   if (!m) return fail(SPADE_EINVAL, "null model");
   if (mode < 0 || mode > 2) return fail(SPADE_EINVAL, "mode must be 0, 1 or 2");
@@ -706,7 +720,7 @@ spade_status spade_tile_tiling(int kind, int rows, int n_units, int k, int n_cu,
   if (kind < GEMM_QKV || kind > GEMM_LM || rows <= kWideMinRows || n_units < 1 || k < 256 || k % 256 != 0 ||
       n_cu < 1)
     return fail(SPADE_EINVAL, "shape out of range");
-  const TileChoice c = tile_choice(kind, rows, n_units, k / 256, n_cu, 0, (size_t)-1);
+  const TileChoice c = tile_choice(kind, rows, n_units, k / 256, n_cu, 0, 0, 0, (size_t)-1);
   *row_tiles = c.rt;
   *panels = c.p;
   *k_splits = c.ks;

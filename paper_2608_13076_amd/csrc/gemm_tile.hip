@@ -2,6 +2,7 @@
 #include "device_gemm_tile.h"
 
 #include <algorithm>
+#include <iterator>
 
 namespace spade {
 namespace {
@@ -111,6 +112,11 @@ constexpr TileCost kTileCosts[] = {{2, 2, 0.362}, {3, 2, 0.418}, {4, 2, 0.479}, 
 
 }  // namespace
 
+bool tile_built(int rt, int p) {
+  return std::any_of(std::begin(kTileCosts), std::end(kTileCosts),
+                     [=](const TileCost& t) { return t.rt == rt && t.p == p; });
+}
+
 // Tile and k-splits of a launch: the least estimate of
 //   rounds of workgroups (one per compute unit at a time, the panel groups of
 //   an XCD on its eighth of them)
@@ -122,14 +128,16 @@ constexpr TileCost kTileCosts[] = {{2, 2, 0.362}, {3, 2, 0.418}, {4, 2, 0.479}, 
 // panel groups pass for one where four XCDs had 36 workgroups for 32 compute
 // units (13B O and down at 144 rows 48 and 97 us, now 39 and 55; 880 rows 150
 // and 363, now 89 and 199); ties to the first tile listed took the 33B LM head
-// at 33 rows 97 us (now 77).  cap_floats: the published values that fit the workspace; fixed_ks > 0: that many splits (one where
-// they do not fit).
-TileChoice tile_choice(int kind, int M, int n_units, int NKB, int n_cu, int fixed_ks, size_t cap_floats) {
+// at 33 rows 97 us (now 77).  cap_floats: the published values that fit the workspace; fixed_rt > 0: that tile (with fixed_p);
+// fixed_ks > 0: that many splits (one where they do not fit).
+TileChoice tile_choice(int kind, int M, int n_units, int NKB, int n_cu, int fixed_rt, int fixed_p, int fixed_ks,
+                       size_t cap_floats) {
   const int tiles = (M + 15) / 16;
   const int xcd_cu = std::max(1, n_cu / 8);
   TileChoice best{2, 2, 1, -1.0};
   double best_cu = 0.0;
   for (const TileCost& t : kTileCosts) {
+    if (fixed_rt > 0 && (t.rt != fixed_rt || t.p != fixed_p)) continue;
     const int nug = gemm_tile_unit_groups(n_units, t.p), nrg = gemm_tile_row_groups(M, t.rt);
     for (int ks = 1; ks <= 8; ++ks) {
       if (kind == GEMM_LM ? ks > 1 : (fixed_ks > 0 && ks != fixed_ks)) continue;
@@ -150,7 +158,7 @@ TileChoice tile_choice(int kind, int M, int n_units, int NKB, int n_cu, int fixe
       }
     }
   }
-  if (best.us < 0) return tile_choice(kind, M, n_units, NKB, n_cu, 1, cap_floats);
+  if (best.us < 0) return tile_choice(kind, M, n_units, NKB, n_cu, fixed_rt, fixed_p, 1, cap_floats);
   return best;
 }
 

@@ -1533,8 +1533,8 @@ hipError_t launch_layer_gemm(spade_model md, spade_kv kv, int kind, int layer, c
       wmat += (size_t)g.unit0 * (K / KBd) * kTileBytes;
       units -= g.unit0;
     }
-    const TileChoice c = tile_choice(kind, M, units, K / KBd, md->n_cu, M <= kTileMidRows ? md->mid_ks : 0,
-                                     W.tile_floats);
+    const int ks = md->tile_ks > 0 ? md->tile_ks : (M <= kTileMidRows ? md->mid_ks : 0);
+    const TileChoice c = tile_choice(kind, M, units, K / KBd, md->n_cu, md->tile_rt, md->tile_p, ks, W.tile_floats);
     GemmParams gp = g;
     gp.w = wmat;
     gp.NKB = K / KBd;

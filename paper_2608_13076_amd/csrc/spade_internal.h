@@ -177,6 +177,7 @@ struct spade_model_s {
   int big_gemm;  // tiled GEMM above 144 rows: 0 chosen, 1 off, 2 every projection of more than 16 rows
   int mid_gemm;  // tiled GEMM of 17 to 144 rows: 0 chosen, 1 off, 2 every projection
   int mid_ks;    // its k-splits: 0 chosen per launch, 1..8 fixed
+  int tile_rt, tile_p, tile_ks;  // tiled GEMM at any rows: tile and k-splits, 0 chosen per launch
 };
 
 struct spade_kv_s {
@@ -239,7 +240,9 @@ struct TileChoice {
   int rt, p, ks;
   double us;
 };
-TileChoice tile_choice(int kind, int M, int n_units, int NKB, int n_cu, int fixed_ks, size_t cap_floats);
+TileChoice tile_choice(int kind, int M, int n_units, int NKB, int n_cu, int fixed_rt, int fixed_p, int fixed_ks,
+                       size_t cap_floats);
+bool tile_built(int rt, int p);
 size_t tile_split_floats();
 struct GemmParams;
 hipError_t launch_tile(int kind, const GemmParams& gp, const TileChoice& c, float* part, hipStream_t st);

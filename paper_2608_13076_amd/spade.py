@@ -39,7 +39,7 @@ EXPORTED_TUNING = (
     "spade_model_set_wide_tiles", "spade_model_set_wide_k_splits", "spade_model_set_split_k",
     "spade_model_set_attn_merge", "spade_model_set_correction_slices", "spade_model_set_attn_grouped",
     "spade_model_set_prefill_rows", "spade_model_set_big_gemm", "spade_model_set_mid_gemm", "spade_profile_gemm",
-    "spade_wide_tiling", "spade_tile_tiling", "spade_model_gemm_engine",
+    "spade_wide_tiling", "spade_tile_tiling", "spade_model_gemm_engine", "spade_model_set_tile_gemm",
 )
 
 
@@ -106,6 +106,7 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
         "spade_model_set_big_gemm": (I, [P, I]),
         "spade_model_set_mid_gemm": (I, [P, I, I]),
         "spade_model_set_split_k": (I, [P, I]),
+        "spade_model_set_tile_gemm": (I, [P, I, I, I]),
         "spade_softmax": (I, [P, I, I, F, P, P]),
         "spade_prefill_batch": (I, [P, P, I, P, I, P, P]),
         "spade_wide_tiling": (I, [I, I, I, I, I, P, P, P]),
@@ -221,6 +222,11 @@ class Model:
         1 off, 2 every projection from 17 rows (not the LM head); k_splits 0
         chosen per launch, 1..8 fixed."""
         _check(self.lib.spade_model_set_mid_gemm(self.handle, int(mode), int(k_splits)))
+
+    def set_tile_gemm(self, row_tiles: int = 0, panels: int = 0, k_splits: int = 0) -> None:
+        """Tile and k-splits of the tiled GEMM wherever it runs; 0 chosen per
+        launch."""
+        _check(self.lib.spade_model_set_tile_gemm(self.handle, int(row_tiles), int(panels), int(k_splits)))
 
     def set_correction_slices(self, mode: int) -> None:
         """Correction draw of sampling requests: 0 or 2 over vocabulary slices

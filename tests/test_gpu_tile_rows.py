@@ -1,8 +1,8 @@
-"""The tiled GEMM over the row counts where its tile changes: 33 to 256 rows of
-a verify call (3- to 9-tile rows, one and two panels a wave, k-splits, ragged
-last tiles; a vocabulary that ends inside a panel) and 300 to
-2040 prompt rows of a prefill forward (128-row tiles), against the wide-row
-GEMM, bit for bit: every engine adds the same eight k-ranges in the same order.
+"""The tiled GEMM as two shapes' calls pick its tile: 33 to 256 rows of a verify
+call (ragged last tiles; a vocabulary that ends inside a panel) and 300 to 2040
+prompt rows of a prefill forward, against the wide-row GEMM, bit for bit: every
+engine adds the same eight k-ranges in the same order.  The picks depend on the
+shape too and leave tiles out; test_gpu_tile_variants.py fixes each in turn.
 """
 
 import numpy as np
