@@ -184,7 +184,7 @@ def kernel_alg_bytes(name: str, w, lens) -> int:
     GEMM's weights once plus its fp32 input and output rows; the attention's
     cached and new K/V rows of one layer."""
     import re
-    name = name.replace("void ", "", 1).replace("spade::", "")
+    name = name.replace("void ", "", 1).replace("spade::", "").replace("(anonymous namespace)::", "")
     m = w.model
     d, f, v = m.d_model, m.d_ffn, m.vocab
     dkv = m.kv_heads * m.head_dim
@@ -198,8 +198,8 @@ def kernel_alg_bytes(name: str, w, lens) -> int:
         kind = int(args[3])
     elif name.startswith("gemm_split_kernel") and len(args) >= 2:
         kind = int(args[1])
-    elif name.startswith("gemm_mid_kernel") and len(args) >= 1:
-        kind = int(args[0])  # the first pass; its second pass (gemm_mid_finish_kernel) counts nothing
+    elif name.startswith("gemm_tile_kernel") and len(args) >= 1:
+        kind = int(args[0])  # a k-split launch's second pass (gemm_tile_finish_kernel) counts nothing
     if kind is not None:
         n_out, k_in = [(d + 2 * dkv, d), (d, d), (2 * f, d), (d, f), (v, d)][kind]
         return n_out * k_in * 2 + M * k_in * 4 + M * (n_out // (2 if kind == 2 else 1)) * 4
@@ -285,14 +285,15 @@ def summarize_step_counters(workload_name: str, dirs, cmds) -> int:
         mb = f"{tf / MFMA_PEAK_TFLOPS:.3f}" if tf is not None else "-"
         hr = f"{100 * hit / (hit + miss):.1f}%" if hit is not None and miss is not None and hit + miss > 0 else "-"
         lb = f"{bank / ldsi:.2f}" if bank is not None and ldsi else "-"
-        short = name.replace("void ", "", 1).replace("spade::", "").split("(")[0]
+        short = name.replace("void ", "", 1).replace("spade::", "").replace("(anonymous namespace)::", "").split("(")[0]
         lines.append(f"| `{short}` | {n} | {us:.1f} | {fmt(alg / 1e6 if alg else None)} | {fmt(rd_b / 1e6 if rd_b else None)} | "
                      f"{fmt(wr_b / 1e6 if wr_b else None)} | {fmt(ratio, 2)} | {fmt(tb, 2)} | {fmt(tf)} | {mb} | {hr} | "
                      f"{lb} | {mm['vgpr']} |")
     lines += ["", "Kernel names: `gemm_wide_kernel<row tiles, panels per wave, kind, k-splits, non-temporal weight loads>`, "
               "`gemm_kernel<bf16, row tiles, operand in LDS, kind>`, `gemm_split_kernel<k-splits, kind>`, "
-              "`gemm_mid_kernel<kind>` (its algorithmic bytes: the whole projection's; the published sums it "
-              "writes and `gemm_mid_finish_kernel<kind>` reads back are traffic beyond them) with kind "
+              "`gemm_tile_kernel<kind, row tiles, panels per wave, k-split, non-temporal weight loads>` (its "
+              "algorithmic bytes: the whole projection's; the sums a k-split launch publishes and "
+              "`gemm_tile_finish_kernel<kind, panels per wave>` reads back are traffic beyond them) with kind "
               "0 QKV, 1 O, 2 gate/up, 3 down, 4 LM head; attention kernels read one layer's K/V.", ""]
     with open(out, "w") as fh:
         fh.write("\n".join(lines))
