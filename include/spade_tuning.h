@@ -42,9 +42,9 @@ spade_status spade_model_set_wide_tiles(spade_model m, int row_tiles, int panels
 
 /* Merge of the verify attention's chunk partials (bf16 cache, head_dim 128:
  * one workgroup per 256-key chunk of a (request, head), each giving a partial
- * -- row max, row sum, unnormalised output -- merged in chunk order).  mode 1: the last workgroup of a
- * (request, head) to finish merges its chunks, which makes every chunk
- * workgroup wait for its stores and an arrival counter; mode 2: the chunk
+ * -- row max, row sum, unnormalised output -- merged in chunk order).  mode 1:
+ * the last workgroup of a (request, head) to finish merges its chunks, which
+ * makes every chunk workgroup wait for its stores and an arrival counter; mode 2: the chunk
  * workgroups store their partials and exit, and a second launch merges each
  * (request, head); mode 0 (the default) chooses per call (mode 2 from four
  * chunks per compute unit).  Results are bit-for-bit the same under every
@@ -55,12 +55,13 @@ spade_status spade_model_set_attn_merge(spade_model m, int mode);
  * from norm(max(0, p - q)), or from p when every draft is accepted; the draw
  * is a Gumbel-max pass over the vocabulary).  mode 0 (the default) or 2: when
  * the call may sample (uniforms given, and draft_probs given or gamma = 0),
- * spade_verify (per-stage path) and spade_accept_from_logits run it in a
+ * spade_verify and spade_accept_from_logits run it in a
  * second launch over slices of 1024 tokens (at most 256 slices), one
  * workgroup per (slice, request), the last slice of a request to finish
  * taking the best of the slices; mode 1 keeps it in the request's accept
  * workgroup.  Results are bit-for-bit the same under every mode (the rows'
- * statistics come from the same launch, whose cut depends on V alone).  Other values return SPADE_EINVAL. */
+ * statistics come from the same launch, whose cut depends on V alone).  Other values return
+ * SPADE_EINVAL. */
 spade_status spade_model_set_correction_slices(spade_model m, int mode);
 
 /* Grouped-query attention chunks.  For a model with G = heads / K/V heads
@@ -88,8 +89,9 @@ spade_status spade_model_set_attn_grouped(spade_model m, int mode);
 spade_status spade_model_set_prefill_rows(spade_model m, int rows);
 
 /* Tiled GEMM of forwards of more than 144 rows (prefill; bf16 weights): a
- * workgroup of eight waves owns up to 144 rows and 256 columns, the activations pass through an LDS ring filled by
- * direct loads and the weights go straight into registers.  mode 0 (the
+ * workgroup of eight waves owns up to 144 rows and 256 columns, the
+ * activations pass through an LDS ring filled by direct loads and the weights
+ * go straight into registers.  mode 0 (the
  * default) uses it for every launch; mode 1 turns it off (the wide-row GEMM
  * runs instead); mode 2 uses it for every projection launch of more than 16
  * rows.  Results are bit-for-bit the same under every mode.  Other values
@@ -155,7 +157,8 @@ spade_status spade_profile_gemm(spade_model m, spade_kv kv, int kind, int B, int
 /* Inspection hook (host only, no device): the tiling the wide-row GEMM picks
  * for a bf16 projection launch of `rows` rows (> 16), `n_units` 16-row weight
  * panels and `k` inputs (a multiple of 256) on `n_cu` compute units, with
- * every setting at its default and buffers large enough for any k-split.
+ * its own settings at their defaults and buffers large enough for any k-split
+ * (more than 32 rows come to it only where the tiled GEMM is turned off).
  * kind as for spade_profile_gemm.  Writes the 16-row tiles per workgroup,
  * the panels per wave and the k-splits; SPADE_EINVAL on a null pointer or
  * a shape out of range. */

@@ -148,7 +148,9 @@ WsPlan plan_ws(const Dims& D, int max_batch, int max_gamma, int max_len) {
   p.split_cnt = take((size_t)p.max_units * 4);
   p.split_part = take((size_t)p.max_units * 8 * 256 * 4);
   // k-split wide-row O and down projections (d / 16 panels, up to Mmax rows):
-  // the most (unit group, row group) items and published floats any tiling needs
+  // the most (unit group, row group) items and published floats any tiling
+  // needs (17 to 32 rows by default; any where a setting keeps larger calls on
+  // that engine, whose k-splits the tests force there)
   if (wb) {
     const int nu = D.d / 16;
     // unit groups of 8 panels (one per wave) x row groups of one 16-row tile

@@ -395,18 +395,11 @@ __device__ __forceinline__ void attn_merge_pair(Rsrc rpo, const AttnMergeSmem& m
   if (ob < nout) out(ob, Ob);
 }
 
-// Publish this chunk's partial (o: the chunk function's result) with write-through
-// stores, arrive on the counter of its (request, head) once the stores have
-// landed, and, in the workgroup that arrives last, merge the request's
-// chunks and pass each merged output o = row * kAttnHd + dd to out(o, value).
-// Merge weights of a row: one wave, chunks over its lanes; the weight of
-// chunk c is exp(m_c - max) / sum_c(l_c exp(m_c - max)).  The last arrival
-// resets the counter.  part_o / part_ml: [bh][NC][Rmax][kAttnHd] /
-// [bh][NC][Rmax][2].  All 512 threads call it; inactive items only
-// synchronise.
 // Store the chunk's partials (o: attn_chunk's result; m / l from sa) with
 // write-through stores, without waiting for them: packed row pr of the rows of
 // query heads h0 .. (R rows each) goes to head h0 + pr / R, row pr % R.
+// part_o / part_ml: [bh][NC][Rmax][kAttnHd] / [bh][NC][Rmax][2].  All 512
+// threads call it.
 template <int CK, int T>
 __device__ __forceinline__ void attn_publish(const AttnItem& it, int h0, const floatx4 (&o)[T], const AttnSmem<CK, T>& sa,
                                              float* part_o, float* part_ml, int H, int NC, int Rmax, int R, int NR) {
@@ -498,7 +491,7 @@ __device__ __forceinline__ void attn_merge_weights(AttnMergeSmem& ms, int nc, in
 template <bool COH, class Out>
 __device__ __forceinline__ void attn_merge(size_t bh, int nc, AttnMergeSmem& ms, float* part_o, float* part_ml,
                                            int NC, int Rmax, int R, Out&& out) {
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x;
   // this thread's first partials, and the (m, l) pairs of the wave's rows
   // (wave and wave + 8: R <= 16), in one round trip
   const Rsrc rpo = wave_rsrc(part_o + (bh * NC * Rmax) * kAttnHd);

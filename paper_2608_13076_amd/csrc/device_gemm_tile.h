@@ -7,11 +7,16 @@
 // tile: RT P MFMA output tiles, each with a running k-range accumulator and a
 // total.  Weights go straight to the one wave that multiplies them, so a
 // 32-k slice costs a compute unit 2 RT KB of activations and 8 P KB of weights
-// from L2 and 16 RT KB of LDS reads for 16 RT P MFMAs.  What bounds it: at
-// P = 2 the L2 path (26 KB per slice at RT = 5; without the MFMAs the 7B
-// gate/up launch of 144 rows takes 72 of its 81 us, without the loads 56), at
-// P = 1 the LDS reads.  Few rows and long weights: RT = 9, P = 1 covers 144
-// rows with one row group; prefill: RT = 6 to 9, P = 2.  Four waves of twice
+// from L2 and 16 RT KB of LDS reads for 16 RT P MFMAs.  What bounds it is what
+// enters the compute unit: all twelve tiles take 17 to 24 ns per KB of
+// 2 RT + 8 P (42 to 58 KB/us, a compute unit's read rate), while pairs of tiles
+// with a third to three times one another's LDS reads take the same time
+// ((6, 1) 96 KB 0.378 us a slice, (2, 2) 32 KB 0.362; (9, 1) 144 KB 0.545,
+// (5, 2) 80 KB 0.560).  Counters of the 7B gate/up launch of 144 rows at (9, 1):
+// on the compute units in use the matrix cores are busy 0.41 of the time and
+// the LDS data path 0.42, without bank conflicts; 69% L2 hits.  Few rows and
+// long weights: RT = 9, P = 1 covers 144 rows with one row group; prefill:
+// RT = 6 to 9, P = 2 (at (8, 2) the MFMAs need 0.61 of a slice's time).  Four waves of twice
 // the panels (one per SIMD, 512 registers) halve the LDS reads and measured
 // 5-10% slower: a lone wave's MFMAs wait behind its own loads.
 //

@@ -35,15 +35,19 @@
 //   attn_prefill_kernel  prefill forwards of more than 16 rows per request:
 //                  one wave per 16-row tile, each tile computed as a verify
 //                  call of its own, K / V^T blocks shared through LDS
-//   accept_kernel  per request: vocabulary-wide max / log-sum-exp / argmax
-//                  per row, the accept chain, the Gumbel-max correction draw
+//   fold_stats_kernel / row_stats_kernel  per row, max / log-sum-exp / argmax
+//                  from the LM head's panels, or of given logits by slices
+//   accept_kernel  per request: the rows' statistics, the accept chain, the
+//                  Gumbel-max correction draw
 //   correct_kernel that draw over vocabulary slices (calls that may sample)
 //   commit_kernel  lens += n + 1, pending = correction
 //   copy_state_kernel / advance_kernel  cache-state copies and single-request
 //                  prefill bookkeeping
 //   prefill_*_kernel   batched prefill: counts and start lengths, token
 //                  gather, advance, pending
-//   softmax_rows_kernel  softmax of logits / T (the draft side of Algorithm 1)
+//   softmax_rows_kernel  softmax of logits / T (the draft side of Algorithm 1),
+//                  long rows over slices of the vocabulary (softmax_slice_,
+//                  softmax_total_, softmax_write_kernel)
 //   pack_kernel    row-major weights -> tiled arena
 #include "device_accept.h"
 #include "device_attn.h"
@@ -738,8 +742,8 @@ __global__ void __launch_bounds__(kAttnThreads) attn_merge_kernel(AttnParams p) 
 // (device_attn.h: attn_prefill_tiles): workgroup (group of W 16-row tiles,
 // query head, request), one wave per tile.  Every tile group and query head
 // of one (request, K/V head) runs on the same XCD, so that pair's keys and
-// values, read by all of them, stay in one L2; on each XCD the groups with
-// the most chunks start first.  Dynamic LDS: attn_prefill_dyn_bytes(W, NC).
+// values, read by all of them, stay in one L2.  Dynamic LDS:
+// attn_prefill_dyn_bytes(W, NS, NC).
 template <bool ABF16, int W, int NS>
 __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2)))
 attn_prefill_kernel(AttnParams p, int ngrp) {
@@ -1364,10 +1368,15 @@ hipError_t launch_wide(spade_model md, int kind, const GemmParams& gp, hipStream
 // govern the tiled GEMM; above, spade_model_set_big_gemm.
 constexpr int kTileMidRows = 144;
 
-// Whether a launch runs on the tiled GEMM by default.  Wide-row against tiled
-// (us per launch): 7B gate/up 39 / 41 at 28 rows, 54 / 47 at 49, 97 / 72 at
-// 144; O 16 / 14, 20 / 17, 31 / 23; 33B gate/up 91 / 93 at 28 rows, 141 / 105
-// at 49; LM heads even at 28 rows, 8B 289 / 197 at 49.
+// Whether a launch runs on the tiled GEMM by default: from the row count at
+// which the wide-row GEMM takes its third 16-row tile.  The four projections of
+// a layer, wide-row / tiled (us): 7B 109 / 112 at 32 rows, 125 / 117 at 33,
+// 126 / 121 at 48, 139 / 129 at 64, 246 / 183 at 144; 13B 144 / 151, 174 / 156,
+// 177 / 164, 197 / 174, 334 / 250; 33B 226 / 238, 256 / 244, 263 / 255, 341 /
+// 275, 494 / 362; 8B 118 / 106, 127 / 109, 129 / 113, 139 / 120, 244 / 168 (the
+// one shape that gains below 33 rows).  Alone, gate/up at 44 to 48 rows (7B 43 /
+// 45, 13B 55 / 60) and QKV at 49 to 64 (13B 43 / 46) are slower tiled.  LM heads
+// are even at 32 rows; at 33 7B 60 / 49, 8B 221 / 188.
 bool tile_wins(int M) { return M > 32; }
 
 // Whether a launch of M rows runs on the tiled GEMM: where it measured faster
@@ -1617,7 +1626,7 @@ hipError_t launch_forward(spade_model md, spade_kv kv, const ForwardCall& fc, hi
   // attention chunks over the longest request: for a bf16 cache with
   // head_dim 128 the 8-wave MFMA kernel, else kAttnChunk
   int max_keys = 0;
-  for (int b = fc.b0; b < fc.b0 + fc.nb; ++b) 
+  for (int b = fc.b0; b < fc.b0 + fc.nb; ++b)
     max_keys = std::max(max_keys, kv->lens_ub[b] + (fc.counts != nullptr ? fc.counts[b - fc.b0] : fc.R));
   const bool tiled = D.kvdt == SPADE_BF16 && D.hd == kAttnHd;
   const bool mfma_attn = tiled && fc.R <= kAttnRows;

@@ -5,7 +5,7 @@ synchronisation while the cache's host length bound covers the call), so a
 caller can capture it.  The graph is replayed several times with eager work
 between the replays (the output buffers cleared, an eager verify call of the
 same inputs, synchronisations); every replay must give the eager call's
-logits and decisions bit for bit.  Shapes: multi-head, wide (the medium-M GEMM
+logits and decisions bit for bit.  Shapes: multi-head, wide (the tiled GEMM
 forced, with its second launch), grouped-query, and the float32 cache.
 """
 

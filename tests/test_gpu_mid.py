@@ -1,12 +1,12 @@
-"""Medium-M projection GEMM (144 rows per workgroup, k-split) against the
+"""Tiled GEMM of batched verification (17 to 144 rows, k-split) against the
 wide-row GEMM.
 
 Every engine sums a dot product over the same eight k-ranges in the same
 order, so a verify call must give bit-identical logits and decisions whichever
-engine runs its projections: here the medium-M engine forced onto calls of
+engine runs its projections: here the tiled engine forced onto calls of
 35 rows (five requests of gamma + 1 = 7; k-blocks fewer than the eight ranges,
-so some ranges and some k-splits are empty) with every k-split count, and at
-its own size, 144 rows (sixteen requests of nine), where the default picks it.
+so some ranges and some k-splits are empty) with several k-split counts, and at
+144 rows (sixteen requests of nine), where the default picks it.
 The wide-row engine these are compared with is checked against the oracle by
 the parity tests.
 """
@@ -51,7 +51,7 @@ def _same(r1, r2, what):
 
 @pytest.mark.parametrize("name", ["mini_bf16_wide_b5", "mini_gqa_mixed_b5"])
 def test_mid_gemm_forced_bit_identical(name):
-    """35 rows: the medium-M engine forced, k-splits 1, 2, 3, 5, 8 and the
+    """35 rows: the tiled engine forced, k-splits 1, 2, 3, 5, 8 and the
     chosen count, against the wide-row engine; the caches written by its QKV
     epilogue are compared through a second verify call."""
     w = MINIS[name]
